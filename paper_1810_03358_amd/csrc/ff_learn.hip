@@ -26,80 +26,435 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
 }
 
 // ------------------------------------------------------------- features
-// One thread per atom: the 16 nearest other atoms of its system by FP64
-// squared distance (ties to the lower index), then
+// Row i of the features:
 //   f[0..2]          = q, sigma - 3.5, 10 eps of the atom,
 //   f[3+7k .. 9+7k]  = (x_j - x_i)/4 (3 values), r/4, q_j, sigma_j - 3.5, 10 eps_j
-// for the k-th neighbour (zeros for missing neighbours), then the place of the
-// atom in its system: (x_i - c)/16 (3 values) and |x_i - c|/16 with c the
+// for its k-th nearest other atom of the same system by FP64 squared distance
+// (ties to the lower index; zeros for missing neighbours), then the place of
+// the atom in its system: (x_i - c)/16 (3 values) and |x_i - c|/16 with c the
 // centroid (a sum in atom order divided by n), and n/4096; zeros up to
 // FF_LEARN_FEATURES.  Each value is rounded FP64 -> FP32 -> BF16.
-__global__ void k_features(const double* __restrict__ xyz, const double* __restrict__ q,
-                           const double* __restrict__ sig, const double* __restrict__ eps,
-                           const int32_t* __restrict__ sys_first, const int32_t* __restrict__ atom_sys, int n_total,
-                           uint16_t* __restrict__ feat, int32_t* __restrict__ nbr) {
-#pragma clang fp contract(off)
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_total) return;
-    const int s = atom_sys[i];
-    const int j0 = sys_first[s], j1 = sys_first[s + 1];
-    const double xi = xyz[3 * (size_t)i], yi = xyz[3 * (size_t)i + 1], zi = xyz[3 * (size_t)i + 2];
-    double bd[FF_LEARN_NEIGHBORS];
-    int bj[FF_LEARN_NEIGHBORS];
+//
+// One launch of two kinds of workgroups that write disjoint bytes:
+//  - one per system sums its coordinates in atom order and writes the three
+//    offsets and their length of every row (centroid_rows);
+//  - one per 16 atoms, each of its wavefronts searching the neighbours of four
+//    (neighbor_rows).
+constexpr int kPlace = 3 + 7 * FF_LEARN_NEIGHBORS;   // first entry of an atom's place in its system
+constexpr int kKnnTile = 256;                        // atoms staged in LDS at a time
+constexpr int kKnnLoads = 3 * kKnnTile / 256;        // ... by so many 8-byte loads of each thread
+
+// DPP move within each row of 16 lanes.
+template <int CTRL, int BANKS = 0xF>
+__device__ __forceinline__ int row_move(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xF, BANKS, false);
+}
+// Value of lane (rank ^ X) of the row.
+template <int X>
+__device__ __forceinline__ int row_xor(int v) {
+    static_assert(X == 1 || X == 2 || X == 3 || X == 4 || X == 7 || X == 8 || X == 15, "rows of 16 lanes");
+    if (X == 1) return row_move<0xB1>(v, v);            // quad_perm [1,0,3,2]
+    if (X == 2) return row_move<0x4E>(v, v);            // quad_perm [2,3,0,1]
+    if (X == 3) return row_move<0x1B>(v, v);            // quad_perm [3,2,1,0]
+    if (X == 4) return row_move<0x114, 0xA>(row_move<0x104, 0x5>(v, v), v);   // row_shl:4 / row_shr:4 by banks
+    if (X == 7) return row_move<0x141>(v, v);           // row_half_mirror
+    if (X == 8) return row_move<0x128>(v, v);           // row_ror:8
+    return row_move<0x140>(v, v);                       // row_mirror
+}
+template <int X>
+__device__ __forceinline__ double row_xor(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = row_xor<X>((int)(b & 0xffffffffLL)), hi = row_xor<X>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// One (distance, index) entry per lane, ordered by distance, then index.
+struct Near { double d; int j; };
+__device__ __forceinline__ bool nearer(const Near& a, const Near& b) {
+    return (a.d < b.d) | ((a.d == b.d) & (a.j < b.j));
+}
+// Compare-exchange of ranks r and r ^ X: the lower rank keeps the nearer entry.
+template <int X>
+__device__ __forceinline__ void order_ranks(Near& e, int rank) {
+    const Near o{row_xor<X>(e.d), row_xor<X>(e.j)};
+    constexpr int top = X >= 8 ? 8 : (X >= 4 ? 4 : (X >= 2 ? 2 : 1));     // highest bit of X
+    const bool take = nearer(o, e) != ((rank & top) != 0);
+    e.d = take ? o.d : e.d;
+    e.j = take ? o.j : e.j;
+}
+// Sorts the 16 entries of each row (bitonic, ten exchanges) and merges them
+// into the row's sorted list, of which the 16 nearest stay (five more).
+__device__ __forceinline__ void merge_row(Near& list, Near e, int rank) {
+    order_ranks<1>(e, rank);
+    order_ranks<3>(e, rank);
+    order_ranks<1>(e, rank);
+    order_ranks<7>(e, rank);
+    order_ranks<2>(e, rank);
+    order_ranks<1>(e, rank);
+    order_ranks<15>(e, rank);
+    order_ranks<4>(e, rank);
+    order_ranks<2>(e, rank);
+    order_ranks<1>(e, rank);
+    const Near o{row_xor<15>(e.d), row_xor<15>(e.j)};
+    const bool take = nearer(o, list);
+    list.d = take ? o.d : list.d;
+    list.j = take ? o.j : list.j;
+    order_ranks<8>(list, rank);
+    order_ranks<4>(list, rank);
+    order_ranks<2>(list, rank);
+    order_ranks<1>(list, rank);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Sums of the workgroup's 256 threads, in every thread.
+__device__ __forceinline__ double block_total(double v, double* red) {
 #pragma unroll
-    for (int k = 0; k < FF_LEARN_NEIGHBORS; ++k) { bd[k] = __builtin_inf(); bj[k] = -1; }
-    double sx = 0.0, sy = 0.0, sz = 0.0;
-    for (int j = j0; j < j1; ++j) {
-        const double xj = xyz[3 * (size_t)j], yj = xyz[3 * (size_t)j + 1], zj = xyz[3 * (size_t)j + 2];
-        sx += xj; sy += yj; sz += zj;
-        if (j == i) continue;
-        const double dx = xj - xi, dy = yj - yi, dz = zj - zi;
-        const double d2 = dx * dx + dy * dy + dz * dz;
-        // candidates arrive in increasing j, so a tie never displaces an entry
-        if (!(d2 < bd[FF_LEARN_NEIGHBORS - 1])) continue;
-        double cd = d2;
-        int cj = j;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// The coordinates of system [j0, j1) summed one by one in atom order: three
+// lanes carry the running sums (x, y, z) over tiles that the whole workgroup
+// stages in LDS, the next tile's loads in flight meanwhile.  Bound by a chain
+// of n dependent FP64 additions (8 ns each).
+__device__ void ordered_sum(const double* __restrict__ x, int n, double (*tile)[3 * kKnnTile], double (&sum)[3]) {
+    const int t = threadIdx.x, n_el = 3 * n;
+    double s = 0.0;
+    double v[kKnnLoads];
 #pragma unroll
-        for (int k = 0; k < FF_LEARN_NEIGHBORS; ++k) {
-            if (cd < bd[k]) {
-                const double td = bd[k];
-                const int tj = bj[k];
-                bd[k] = cd; bj[k] = cj;
-                cd = td; cj = tj;
+    for (int c = 0; c < kKnnLoads; ++c) v[c] = t + c * 256 < n_el ? x[t + c * 256] : 0.0;
+    int buf = 0;
+    for (int a0 = 0; a0 < n; a0 += kKnnTile, buf ^= 1) {
+#pragma unroll
+        for (int c = 0; c < kKnnLoads; ++c) tile[buf][t + c * 256] = v[c];
+        __syncthreads();
+        const int e0 = 3 * (a0 + kKnnTile) + t;
+#pragma unroll
+        for (int c = 0; c < kKnnLoads; ++c) v[c] = e0 + c * 256 < n_el ? x[e0 + c * 256] : 0.0;
+        if (t < 3) {
+            const double* p = tile[buf] + t;
+            const int m = min(kKnnTile, n - a0);
+            int a = 0;
+            for (; a + 16 <= m; a += 16) {
+                double w[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) w[k] = p[3 * (a + k)];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) s += w[k];
             }
+            for (; a < m; ++a) s += p[3 * a];
         }
     }
-    uint16_t* f = feat + (size_t)i * FF_LEARN_FEATURES;
-    f[0] = to_bf16((float)q[i]);
-    f[1] = to_bf16((float)(sig[i] - 3.5));
-    f[2] = to_bf16((float)(10.0 * eps[i]));
+    __syncthreads();
+    if (t < 3) tile[0][t] = s;
+    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < FF_LEARN_NEIGHBORS; ++k) {
-        const int j = bj[k];
-        uint16_t* g = f + 3 + 7 * k;
-        if (nbr) nbr[(size_t)i * FF_LEARN_NEIGHBORS + k] = j;
+    for (int c = 0; c < 3; ++c) sum[c] = tile[0][c];
+}
+
+// Place entries of the rows of system [j0, j1), from its coordinate sums.
+// With err > 0 the sums may be off by that much from the ordered ones: the
+// return value says whether an entry of this thread's rows could then round
+// to another BF16 value.
+__device__ bool place_rows(const double* __restrict__ x, int n, const double (&sum)[3], double err,
+                           uint16_t* __restrict__ feat) {
+#pragma clang fp contract(off)
+    const double nd = (double)n;
+    const double c0 = sum[0] / nd, c1 = sum[1] / nd, c2 = sum[2] / nd;
+    bool unsure = false;
+#pragma unroll 4
+    for (int a = threadIdx.x; a < n; a += 256) {
+        const double px = x[3 * (size_t)a], py = x[3 * (size_t)a + 1], pz = x[3 * (size_t)a + 2];
+        const double cx = px - c0, cy = py - c1, cz = pz - c2;
+        const double v[4] = {cx / 16.0, cy / 16.0, cz / 16.0, sqrt(cx * cx + cy * cy + cz * cz) / 16.0};
+        uint16_t* h = feat + (size_t)a * FF_LEARN_FEATURES + kPlace;
+        // sum error through the division, the difference, the length and /16
+        // (and the rounding of each)
+        const double e = 0.25 * (err / nd) +
+                         0x1p-48 * (fabs(px) + fabs(py) + fabs(pz) + fabs(c0) + fabs(c1) + fabs(c2));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint16_t b = to_bf16((float)v[k]);
+            h[k] = b;
+            if (err > 0.0) unsure |= to_bf16((float)(v[k] - e)) != b || to_bf16((float)(v[k] + e)) != b;
+        }
+    }
+    return unsure;
+}
+
+// The centroid is defined by the ordered sum, whose dependent additions would
+// take longer than the neighbour search beside it (80 us at 10,000 atoms), but
+// only BF16 roundings of its offsets are wanted.  So the workgroup sums in
+// parallel and bounds the difference: either order is within n u sum|x| of
+// the exact sum (u = 2^-53), so they differ by less than err = n 2^-51 sum|x|.
+// Where every entry rounds alike over that range the rows hold what the
+// ordered sum gives; else (some 1e-3 of 10,000-atom systems) it is formed.
+__device__ void centroid_rows(const double* __restrict__ xyz, int j0, int j1, uint16_t* __restrict__ feat,
+                              double (*tile)[3 * kKnnTile]) {
+#pragma clang fp contract(off)
+    const int t = threadIdx.x, n = j1 - j0, n_el = 3 * n;
+    if (n < 1) return;
+    const double* x = xyz + 3 * (size_t)j0;
+    uint16_t* rows = feat + (size_t)j0 * FF_LEARN_FEATURES;
+    // elements t + 256 (3 k + c) of the flat array are component (t + c) mod 3
+    double part[3] = {0.0, 0.0, 0.0}, mag = 0.0;
+#pragma unroll 4
+    for (int e = t; e < n_el; e += 3 * 256)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double v = e + c * 256 < n_el ? x[e + c * 256] : 0.0;
+            part[c] += v;
+            mag += fabs(v);
+        }
+    const int r = t % 3;
+    double sum[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) sum[c] = block_total(r == c ? part[0] : ((r + 1) % 3 == c ? part[1] : part[2]), tile[0]);
+    const double err = block_total(mag, tile[0]) * ((double)n * 0x1p-51);
+    __syncthreads();
+    bool unsure = !(err > 0.0 && err <= __DBL_MAX__);
+    if (!unsure) unsure = place_rows(x, n, sum, err, rows);
+    if (!__syncthreads_or(unsure)) return;
+    ordered_sum(x, n, tile, sum);
+    place_rows(x, n, sum, 0.0, rows);
+}
+
+// Neighbours and row entries of atoms [a0, a0 + 16), four per wavefront.  A
+// lane takes one candidate of 64 at a time for each of the four atoms; those
+// not farther than an atom's 16th nearest so far go to its queue in LDS.  Once
+// a queue holds 16, the last 16 of every queue are merged into the atoms'
+// lists, which lie sorted in the 16 lanes of row k for atom k: one merge
+// serves four atoms.  The order is total (distance, then index), so the
+// result does not depend on the order of candidates, and the search starts
+// around the atoms themselves: chain neighbours set a tight limit before the rest is
+// scanned.
+// Bound by VALU issue of the first pass (30 instructions per 64 candidates and
+// four atoms) and below a few thousand atoms by latency.  10,000 atoms: 67 us,
+// against 1.81 ms for one thread per atom scanning every candidate, which left
+// 157 wavefronts on 1,024 SIMDs; 50,000 atoms 0.73 ms, 300 atoms 14 us.
+// Inserting candidates one by one through scalar registers instead of merging
+// 16 took 2-3 times as long below 4,000 atoms; testing all of them in FP64,
+// without the FP32 pass, 0.99 ms at 50,000 atoms.
+constexpr int kKnnAtoms = 4;                         // atoms per wavefront: one per row of 16 lanes
+constexpr int kKnnQueue = 64 + 16;                   // candidates waiting per atom: at most 15 + 64
+
+__device__ void neighbor_rows(const double* __restrict__ xyz, const double* __restrict__ q,
+                              const double* __restrict__ sig, const double* __restrict__ eps,
+                              const int32_t* __restrict__ sys_first, const int32_t* __restrict__ atom_sys, int a0,
+                              int n_total, uint16_t* __restrict__ feat, int32_t* __restrict__ nbr,
+                              double (*tile)[3 * kKnnTile], double* __restrict__ queue_d,
+                              int* __restrict__ queue_j, uint16_t* __restrict__ rowbuf) {
+#pragma clang fp contract(off)
+    constexpr int A = kKnnAtoms;
+    const int t = threadIdx.x, lane = t & 63, rank = t & 15, row = (t & 63) >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int last = min(a0 + 4 * A, n_total) - 1;
+    const int s_lo = atom_sys[a0], s_hi = atom_sys[last];
+    const int lo = sys_first[s_lo], hi = sys_first[s_hi + 1];   // candidates of all of the workgroup's atoms
+    const bool mixed = s_lo != s_hi;                            // ... which then differ from atom to atom
+    const int n_c = hi - lo, n_el = 3 * n_c;
+    const int n_tiles = (n_c + kKnnTile - 1) / kKnnTile;
+    const double* x = xyz + 3 * (size_t)lo;
+    int ai[A], jb[A], je[A];
+    double xi[A], yi[A], zi[A], limit[A];
+#pragma unroll
+    for (int k = 0; k < A; ++k) {
+        const int i = min(a0 + wave * A + k, n_total - 1);      // (rows past the end are not written)
+        const int s = mixed ? atom_sys[i] : s_lo;
+        ai[k] = i - lo;
+        jb[k] = sys_first[s] - lo;
+        je[k] = sys_first[s + 1] - lo;
+        xi[k] = xyz[3 * (size_t)i]; yi[k] = xyz[3 * (size_t)i + 1]; zi[k] = xyz[3 * (size_t)i + 2];
+        limit[k] = __DBL_MAX__;                                 // candidates have finite distances
+    }
+    Near list{__builtin_inf(), -1};                             // entry `rank` of row's atom
+    double* qd = queue_d + wave * A * kKnnQueue;
+    int* qj = queue_j + wave * A * kKnnQueue;
+    int waiting[A] = {};
+    // the last 16 entries of every queue (missing ones: infinity) into the lists
+    auto merge = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        int at = 0, end = 0;
+#pragma unroll
+        for (int k = 0; k < A; ++k) {
+            const int first = max(waiting[k] - 16, 0);
+            at = row == k ? first : at;
+            end = row == k ? waiting[k] : end;
+            waiting[k] = first;
+        }
+        at += rank;
+        Near e{__builtin_inf(), -1};
+        if (at < end) e = Near{qd[row * kKnnQueue + at], qj[row * kKnnQueue + at]};
+        merge_row(list, e, rank);
+#pragma unroll
+        for (int k = 0; k < A; ++k) limit[k] = fmin(lane_value(list.d, 16 * k + 15), __DBL_MAX__);
+    };
+    // First pass: FP32 tests |x_j|^2 - 2 x_i.x_j <= limit - |x_i|^2 in
+    // coordinates relative to the wavefront's first atom.  A candidate at
+    // distance d <= r = sqrt(limit) of atom i, itself ro from the first, lies
+    // within r + ro of it, so coordinates, products and sums round by less than
+    // 2^-18 (r + 2 ro)^2 in all: the test with that margin misses none.
+    float xf[A], yf[A], zf[A], bound[A];
+    double ro[A];
+#pragma unroll
+    for (int k = 0; k < A; ++k) {
+        const double dx = xi[k] - xi[0], dy = yi[k] - yi[0], dz = zi[k] - zi[0];
+        xf[k] = (float)(-2.0 * dx); yf[k] = (float)(-2.0 * dy); zf[k] = (float)(-2.0 * dz);
+        ro[k] = dx * dx + dy * dy + dz * dz;
+        bound[k] = __builtin_inff();
+    }
+    auto pass_bounds = [&]() {
+#pragma unroll
+        for (int k = 0; k < A; ++k) {
+            const double r = sqrt(limit[k]) + 2.0 * sqrt(ro[k]);
+            bound[k] = (float)(limit[k] - ro[k] + 0x1p-18 * (r * r)) + 0x1p-100f;      // (+: FP32 underflow)
+        }
+    };
+    // candidate c is atom (start + c) mod n_c: the first tile lies around the
+    // workgroup's atoms.  The loads of the next two tiles are in flight (without
+    // a branch around them: the wait for one must not include the next);
+    // candidates past the end are NaN, which the second pass never admits.
+    const int start = max(0, min(a0 - lo - (kKnnTile - 16) / 2, n_c - kKnnTile));
+    auto load = [&](int step, double (&v)[kKnnLoads]) {
+        const int e0 = 3 * kKnnTile * step + t;
+#pragma unroll
+        for (int c = 0; c < kKnnLoads; ++c) {
+            const int e = min(e0 + c * 256, n_el - 1) + 3 * start;
+            v[c] = x[e >= n_el ? e - n_el : e];
+        }
+    };
+    auto scan = [&](int step, double (&v)[kKnnLoads]) {
+        const int base = step * kKnnTile, buf = step & 1;
+#pragma unroll
+        for (int c = 0; c < kKnnLoads; ++c)
+            tile[buf][c * 256 + t] = 3 * base + c * 256 + t < n_el ? v[c] : __builtin_nan("");
+        __syncthreads();
+        load(step + 2, v);
+        // first pass: which 64 candidates may hold one for any of the four atoms
+        unsigned hit = 0;
+#pragma unroll
+        for (int no = 0; no < kKnnTile / 64; ++no) {
+            const double* p = tile[buf] + 3 * (no * 64 + lane);
+            const float xj = (float)(p[0] - xi[0]), yj = (float)(p[1] - yi[0]), zj = (float)(p[2] - zi[0]);
+            const float rr = __fmaf_rn(zj, zj, __fmaf_rn(yj, yj, xj * xj));
+            bool near = false;
+#pragma unroll
+            for (int k = 0; k < A; ++k)
+                near |= !(__fmaf_rn(zf[k], zj, __fmaf_rn(yf[k], yj, __fmaf_rn(xf[k], xj, rr))) > bound[k]);
+            hit |= (__ballot(near) && base + no * 64 < n_c ? 1u : 0u) << no;
+        }
+        // second pass over those (the atoms' own first): into the queues
+        const int own = step == 0 ? (ai[0] - start) >> 6 : 0;
+#pragma unroll 1
+        for (int s4 = 0; s4 < kKnnTile / 64; ++s4) {
+            const int no = (s4 + own) & (kKnnTile / 64 - 1);
+            if (!((hit >> no) & 1u)) continue;
+            const int sub = no * 64, c0 = base + sub;
+            const int jw = start + c0 + lane, j = jw >= n_c ? jw - n_c : jw;     // (used below n_c only)
+            const double* p = tile[buf] + 3 * (sub + lane);
+            const double xj = p[0], yj = p[1], zj = p[2];
+            double d2[A];
+            unsigned long long m[A];
+#pragma unroll
+            for (int k = 0; k < A; ++k) {
+                const double dx = xj - xi[k], dy = yj - yi[k], dz = zj - zi[k];
+                d2[k] = dx * dx + dy * dy + dz * dz;
+                m[k] = __ballot(d2[k] <= limit[k]);
+                const int self = (ai[k] >= start ? ai[k] - start : ai[k] - start + n_c) - c0;
+                if (self >= 0 && self < 64) m[k] &= ~(1ull << self);
+                if (mixed) m[k] &= __ballot(j >= jb[k] && j < je[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < A; ++k) {
+                if ((m[k] >> lane) & 1ull) {
+                    const int at = k * kKnnQueue + waiting[k] + __popcll(m[k] & ((1ull << lane) - 1ull));
+                    qd[at] = d2[k];
+                    qj[at] = j;
+                }
+                waiting[k] += __popcll(m[k]);
+            }
+            while (max(max(waiting[0], waiting[1]), max(waiting[2], waiting[3])) >= 16) merge();
+        }
+        if (hit) pass_bounds();
+    };
+    double va[kKnnLoads], vb[kKnnLoads];
+    load(0, va);
+    load(1, vb);
+    for (int step = 0; step < n_tiles; step += 2) {
+        scan(step, va);
+        if (step + 1 < n_tiles) scan(step + 1, vb);
+    }
+    if (waiting[0] | waiting[1] | waiting[2] | waiting[3]) merge();
+    // row k writes atom k's row into LDS; it is stored as 32-bit words but for
+    // the entries of the atom's place, which the centroid workgroup writes
+    uint16_t* rows = rowbuf + wave * A * FF_LEARN_FEATURES;
+    const int i = a0 + wave * A + row;
+    if (i <= last) {
+        uint16_t* f = rows + row * FF_LEARN_FEATURES;
+        uint16_t* g = f + 3 + 7 * rank;
+        const int j = list.j < 0 ? -1 : lo + list.j;
+        if (nbr) nbr[(size_t)i * FF_LEARN_NEIGHBORS + rank] = j;
         if (j < 0) {
             for (int c = 0; c < 7; ++c) g[c] = 0;
-            continue;
+        } else {
+            const double dx = xyz[3 * (size_t)j] - xyz[3 * (size_t)i], dy = xyz[3 * (size_t)j + 1] - xyz[3 * (size_t)i + 1],
+                         dz = xyz[3 * (size_t)j + 2] - xyz[3 * (size_t)i + 2];
+            g[0] = to_bf16((float)(dx / 4.0));
+            g[1] = to_bf16((float)(dy / 4.0));
+            g[2] = to_bf16((float)(dz / 4.0));
+            g[3] = to_bf16((float)(sqrt(list.d) / 4.0));
+            g[4] = to_bf16((float)q[j]);
+            g[5] = to_bf16((float)(sig[j] - 3.5));
+            g[6] = to_bf16((float)(10.0 * eps[j]));
         }
-        const double dx = xyz[3 * (size_t)j] - xi, dy = xyz[3 * (size_t)j + 1] - yi, dz = xyz[3 * (size_t)j + 2] - zi;
-        g[0] = to_bf16((float)(dx / 4.0));
-        g[1] = to_bf16((float)(dy / 4.0));
-        g[2] = to_bf16((float)(dz / 4.0));
-        g[3] = to_bf16((float)(sqrt(bd[k]) / 4.0));
-        g[4] = to_bf16((float)q[j]);
-        g[5] = to_bf16((float)(sig[j] - 3.5));
-        g[6] = to_bf16((float)(10.0 * eps[j]));
+        const int s = mixed ? atom_sys[i] : s_lo;
+        if (rank == 0) f[0] = to_bf16((float)q[i]);
+        if (rank == 1) f[1] = to_bf16((float)(sig[i] - 3.5));
+        if (rank == 2) f[2] = to_bf16((float)(10.0 * eps[i]));
+        if (rank == 3) f[kPlace + 4] = to_bf16((float)((double)(sys_first[s + 1] - sys_first[s]) / 4096.0));
+        if (rank >= 4 && rank < 4 + FF_LEARN_FEATURES - (kPlace + 5)) f[kPlace + 5 + rank - 4] = 0;
     }
-    const double n = (double)(j1 - j0);
-    const double cx = xi - sx / n, cy = yi - sy / n, cz = zi - sz / n;
-    uint16_t* h = f + 3 + 7 * FF_LEARN_NEIGHBORS;
-    h[0] = to_bf16((float)(cx / 16.0));
-    h[1] = to_bf16((float)(cy / 16.0));
-    h[2] = to_bf16((float)(cz / 16.0));
-    h[3] = to_bf16((float)(sqrt(cx * cx + cy * cy + cz * cz) / 16.0));
-    h[4] = to_bf16((float)(n / 4096.0));
-    for (int c = 8 + 7 * FF_LEARN_NEIGHBORS; c < FF_LEARN_FEATURES; ++c) f[c] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int k = 0; k < A && a0 + wave * A + k <= last; ++k) {
+        const uint16_t* r = rows + k * FF_LEARN_FEATURES;
+        uint16_t* f = feat + (size_t)(a0 + wave * A + k) * FF_LEARN_FEATURES;
+        constexpr int w_lo = kPlace / 2, w_hi = (kPlace + 4) / 2;   // first and last word shared with the place
+        if (lane < w_lo || lane > w_hi) ((uint32_t*)f)[lane] = ((const uint32_t*)r)[lane];
+        else if (lane == w_lo) f[2 * w_lo] = r[2 * w_lo];
+        else if (lane == w_hi) f[2 * w_hi + 1] = r[2 * w_hi + 1];
+    }
+}
+
+// Grid: n_sys centroid workgroups, then one per 4 * kKnnAtoms atoms.
+__global__ void __launch_bounds__(256) k_features(const double* __restrict__ xyz, const double* __restrict__ q,
+                                                  const double* __restrict__ sig, const double* __restrict__ eps,
+                                                  const int32_t* __restrict__ sys_first,
+                                                  const int32_t* __restrict__ atom_sys, int n_sys, int n_total,
+                                                  uint16_t* __restrict__ feat, int32_t* __restrict__ nbr) {
+    static_assert(kPlace % 2 == 1 && FF_LEARN_FEATURES == 128, "row words of the place entries");
+    __shared__ double tile[2][3 * kKnnTile];
+    __shared__ double queue_d[4 * kKnnAtoms * kKnnQueue];
+    __shared__ int queue_j[4 * kKnnAtoms * kKnnQueue];
+    __shared__ __attribute__((aligned(4))) uint16_t rowbuf[4 * kKnnAtoms * FF_LEARN_FEATURES];
+    const int b = blockIdx.x;
+    if (b < n_sys)
+        centroid_rows(xyz, sys_first[b], sys_first[b + 1], feat, tile);
+    else
+        neighbor_rows(xyz, q, sig, eps, sys_first, atom_sys, (b - n_sys) * 4 * kKnnAtoms, n_total, feat, nbr, tile,
+                      queue_d, queue_j, rowbuf);
 }
 
 // ------------------------------------------------------------------ GEMM
@@ -508,8 +863,9 @@ ff_status ff_learn_features(int32_t n_sys, int32_t n_total, const double* xyz, c
     g_learn_err.clear();
     if (n_sys < 1 || n_total < 1) return lfail(FF_ERR_ARG, "need at least one system and one atom");
     if (!xyz || !q || !sigma || !eps || !sys_first || !atom_sys || !features) return lfail(FF_ERR_ARG, "null pointer");
-    hipLaunchKernelGGL(k_features, dim3((n_total + 127) / 128), dim3(128), 0, (hipStream_t)stream, xyz, q, sigma,
-                       eps, sys_first, atom_sys, n_total, features, neighbors);
+    const int blocks = n_sys + (n_total + 4 * kKnnAtoms - 1) / (4 * kKnnAtoms);
+    hipLaunchKernelGGL(k_features, dim3(blocks), dim3(256), 0, (hipStream_t)stream, xyz, q, sigma, eps,
+                       sys_first, atom_sys, n_sys, n_total, features, neighbors);
     L_TRY(hipGetLastError());
     return FF_OK;
 }
