@@ -44,9 +44,9 @@ extern "C" {
 int32_t ff_learn_param_count(void);
 
 /* Device workspace for ff_learn_forward and ff_learn_backward with up to
- * n_rows rows (the forward pass uses its first part: the activations; the
- * backward pass also holds their gradients and 4 MiB of per-slice partial
- * sums for the weight gradients).  0 for n_rows < 1. */
+ * n_rows rows (the backward pass keeps its partial sums of the gradient there;
+ * with arrays that its fused kernels cannot read, activations, their
+ * gradients and 4 MiB of per-slice partial sums).  0 for n_rows < 1. */
 size_t ff_learn_workspace_bytes(int32_t n_rows);
 
 /* Description of the last error of an ff_learn_* call on this thread. */

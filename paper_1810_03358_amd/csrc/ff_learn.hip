@@ -675,6 +675,442 @@ hipError_t launch_gemm(int m, int n, int k, const uint16_t* A, long sa0, long sa
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ network
+// Parameter offsets (elements) in the packed vector.
+constexpr long kW1 = 0, kB1 = kW1 + (long)FF_LEARN_FEATURES * FF_LEARN_HIDDEN;
+constexpr long kW2 = kB1 + FF_LEARN_HIDDEN, kB2 = kW2 + (long)FF_LEARN_HIDDEN * FF_LEARN_HIDDEN;
+constexpr long kW3 = kB2 + FF_LEARN_HIDDEN, kB3 = kW3 + (long)FF_LEARN_HIDDEN * FF_LEARN_OUT_PAD;
+constexpr long kParams = kB3 + FF_LEARN_OUT_PAD;
+static_assert(FF_LEARN_FEATURES == 128 && FF_LEARN_HIDDEN == 128 && FF_LEARN_OUT_PAD == 16,
+              "fragment counts of the fused network");
+
+// The three layers of 16 rows run in the registers of one wavefront.  The
+// matrix-core fragments of both operands hold index l % 16 and k = 4 (l / 16) + q
+// in lane l, and a product comes back with its second operand's index at l % 16
+// and the first's at 4 (l / 16) + q.  So with the weights as the first operand
+// (and the rows as the second) the activations of one layer, rounded to BF16,
+// are the operand of the next; with the operands exchanged they come back with
+// the roles of row and column exchanged, which is what the weight gradients
+// contract over.  k runs in the same order as in k_gemm.
+constexpr int kT = 8;                        // 16-wide tiles of a 128-wide layer
+constexpr int kLdw = 128 + 8;                // weights in LDS: [output][input], padded against bank conflicts
+constexpr int kRowBlock = 64;                // rows of a workgroup at a time: 16 per wavefront
+
+typedef __bf16 hwbf16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x4_t pack_bf16(const f32x4_t& v) {          // v_cvt_pk_bf16_f32: nearest even
+    return __builtin_bit_cast(bf16x4_t, __builtin_convertvector(v, hwbf16x4_t));
+}
+__device__ __forceinline__ f32x4_t mfma16(const bf16x4_t& a, const bf16x4_t& b, const f32x4_t& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+
+// W [128][COLS] (row-major, BF16) through registers into LDS as [COLS][kLdw]
+// (store) and, where wanted, also as it is with rows of kLdw (store_rows).  A
+// thread takes 4 x 4 elements at a time; the 8 x 8 pattern of a wavefront keeps
+// the writes free of bank conflicts.  The loads of all weights are issued
+// before the first store: one memory latency, not one for each.
+template <int COLS>
+struct StagedWeights {
+    static constexpr int kTasks = 32 * (COLS / 4);
+    static constexpr int kPer = (kTasks + 255) / 256;
+    uint2 w[kPer][4];
+    __device__ __forceinline__ static int column(int task) {
+        return COLS == 128 ? 4 * (((task >> 6) & 3) * 8 + (task & 7)) : 4 * (task & 3);
+    }
+    __device__ __forceinline__ static int row(int task) {
+        return COLS == 128 ? 4 * ((task >> 8) * 8 + ((task >> 3) & 7)) : 4 * ((task >> 2) & 31);
+    }
+    __device__ __forceinline__ void load(const uint16_t* __restrict__ W) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int task = threadIdx.x + 256 * i;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (task < kTasks) w[i][q] = *(const uint2*)(W + (row(task) + q) * COLS + column(task));
+        }
+    }
+    __device__ __forceinline__ void store(uint16_t* __restrict__ lds) const {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int task = threadIdx.x + 256 * i;
+            if (task >= kTasks) continue;
+            uint16_t* p = lds + column(task) * kLdw + row(task);
+            const uint2(&v)[4] = w[i];
+            *(uint2*)(p) = make_uint2((v[0].x & 0xffffu) | (v[1].x << 16), (v[2].x & 0xffffu) | (v[3].x << 16));
+            *(uint2*)(p + kLdw) = make_uint2((v[0].x >> 16) | (v[1].x & 0xffff0000u), (v[2].x >> 16) | (v[3].x & 0xffff0000u));
+            *(uint2*)(p + 2 * kLdw) = make_uint2((v[0].y & 0xffffu) | (v[1].y << 16), (v[2].y & 0xffffu) | (v[3].y << 16));
+            *(uint2*)(p + 3 * kLdw) = make_uint2((v[0].y >> 16) | (v[1].y & 0xffff0000u), (v[2].y >> 16) | (v[3].y & 0xffff0000u));
+        }
+    }
+    __device__ __forceinline__ void store_rows(uint16_t* __restrict__ lds) const {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int task = threadIdx.x + 256 * i;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (task < kTasks) *(uint2*)(lds + (row(task) + q) * kLdw + column(task)) = w[i][q];
+        }
+    }
+};
+// Fragment of the staged weights: output tile nt, input tile kt.
+__device__ __forceinline__ bf16x4_t weight_frag(const uint16_t* lds, int nt, int kt, int l) {
+    return *(const bf16x4_t*)(lds + (nt * 16 + (l & 15)) * kLdw + kt * 16 + 4 * (l >> 4));
+}
+
+// Bias, ReLU and BF16 of one tile; the bits of the positive values go to
+// positive[4 t ..].
+__device__ __forceinline__ bf16x4_t relu_tile(f32x4_t acc, const f32x4_t& b, int t, uint32_t& positive) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        acc[q] = fmaxf(acc[q] + b[q], 0.0f);
+        if (acc[q] > 0.0f) positive |= 1u << (4 * t + q);
+    }
+    return pack_bf16(acc);
+}
+// A hidden layer of the wavefront's rows.  `out`: the next layer's operand (the
+// lane's row at l % 16).  BOTH: also with the operands exchanged, `by_rows`
+// (rows 4 (l / 16) + q at unit l % 16 of each tile); both from one read of the
+// weights.  The masks hold the positive activations.
+template <bool BOTH>
+__device__ __forceinline__ void hidden_layer(const uint16_t* w, const float* __restrict__ bias, const bf16x4_t (&in)[kT],
+                                             int l, bf16x4_t (&out)[kT], uint32_t& positive, bf16x4_t (&by_rows)[kT],
+                                             uint32_t& positive_rows) {
+    positive = positive_rows = 0;
+#pragma unroll
+    for (int n0 = 0; n0 < kT; n0 += 4) {
+        f32x4_t acc[4] = {}, acr[4] = {};
+#pragma unroll
+        for (int kt = 0; kt < kT; ++kt)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bf16x4_t f = weight_frag(w, n0 + u, kt, l);
+                acc[u] = mfma16(f, in[kt], acc[u]);
+                if (BOTH) acr[u] = mfma16(in[kt], f, acr[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int t = n0 + u;
+            out[t] = relu_tile(acc[u], *(const f32x4_t*)(bias + t * 16 + 4 * (l >> 4)), t, positive);
+            if (BOTH) {
+                const float b = bias[t * 16 + (l & 15)];
+                by_rows[t] = relu_tile(acr[u], f32x4_t{b, b, b, b}, t, positive_rows);
+            }
+        }
+    }
+}
+__device__ __forceinline__ void load_biases(const float* __restrict__ params, float* bias) {
+    for (int k = threadIdx.x; k < 272; k += 256)
+        bias[k] = params[k < 128 ? kB1 + k : (k < 256 ? kB2 + k - 128 : kB3 + k - 256)];
+}
+
+// BF16 feature fragments of row `row` (zeros past the end).
+__device__ __forceinline__ void load_rows(const uint16_t* __restrict__ X, int row, int n, int l, bf16x4_t (&x)[kT]) {
+    const uint16_t* p = X + (size_t)min(row, n - 1) * FF_LEARN_FEATURES + 4 * (l >> 4);
+#pragma unroll
+    for (int kt = 0; kt < kT; ++kt) x[kt] = *(const bf16x4_t*)(p + kt * 16);
+    if (row >= n)
+#pragma unroll
+        for (int kt = 0; kt < kT; ++kt) x[kt] = bf16x4_t{0, 0, 0, 0};
+}
+
+// Network output of every row: one launch, weights staged once per workgroup,
+// activations in registers.  Bound by latency (weights, then two layers): 7.5 us
+// at 10,000 rows; three products with BF16 and FP32 activations in memory
+// between them took 32 us.
+constexpr int kForwardGrid = 512;            // two workgroups of 74 KB LDS per CU
+__global__ void __launch_bounds__(256, 2) k_forward(const float* __restrict__ params, const uint16_t* __restrict__ wb,
+                                                 const uint16_t* __restrict__ X, int n, float* __restrict__ Y) {
+    __shared__ __attribute__((aligned(16))) uint16_t w1[128 * kLdw], w2[128 * kLdw], w3[16 * kLdw];
+    __shared__ __attribute__((aligned(16))) float bias[272];
+    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    bf16x4_t x[kT], h1[kT], h2[kT], none[kT];
+    load_rows(X, blockIdx.x * kRowBlock + wave * 16 + (l & 15), n, l, x);
+    {
+        StagedWeights<128> s1, s2;
+        StagedWeights<16> s3;
+        s1.load(wb + kW1);
+        s2.load(wb + kW2);
+        s3.load(wb + kW3);
+        load_biases(params, bias);
+        s1.store(w1);
+        s2.store(w2);
+        s3.store(w3);
+    }
+    __syncthreads();
+    for (int r0 = blockIdx.x * kRowBlock; r0 < n; r0 += gridDim.x * kRowBlock) {
+        // weights are read again for each row block (kept across the loop they
+        // would fill the registers)
+        asm volatile("" : : : "memory");
+        const int row = r0 + wave * 16 + (l & 15);
+        uint32_t mask, mask_rows;
+        hidden_layer<false>(w1, bias, x, l, h1, mask, none, mask_rows);
+        if (r0 + (int)gridDim.x * kRowBlock < n) load_rows(X, row + gridDim.x * kRowBlock, n, l, x);
+        hidden_layer<false>(w2, bias + 128, h1, l, h2, mask, none, mask_rows);
+        f32x4_t y = {};
+#pragma unroll
+        for (int kt = 0; kt < kT; ++kt) y = mfma16(weight_frag(w3, 0, kt, l), h2[kt], y);
+        y += *(const f32x4_t*)(bias + 256 + 4 * (l >> 4));
+        if (row < n) *(f32x4_t*)(Y + (size_t)row * FF_LEARN_OUT_PAD + 4 * (l >> 4)) = y;
+    }
+}
+
+// Forward and backward pass of one minibatch up to per-workgroup partial sums
+// of the gradient: one launch, then k_gradient_sum.  A wavefront computes the
+// activations and their gradients of its 16 rows in registers, in both
+// orientations (see above): the one with the lane's row at l % 16 feeds the next
+// product, the other one (rows at 4 (l / 16) + q) goes to LDS as a fragment.
+// Then wavefront w forms the weight gradients of input tiles 2w and 2w + 1 over
+// the workgroup's 64 rows, which stay in its registers over all of its row
+// blocks.  Bias gradients and the loss are summed in FP64.
+// 8,192 rows: 26 us and 5.6 us for the sum, of which 4.5 us stage the weights,
+// 10 us are products and 3.6 us the store of the partials (18 MB); 15 launches
+// with every activation and gradient in memory in FP32 and BF16 took 150 us.
+constexpr int kTrainGrid = 256;              // one workgroup of 159 KB LDS per CU
+constexpr int kBiasSums = 128 + 128 + 16 + 1;         // FP64 partials of a workgroup: db1, db2, db3, loss
+constexpr size_t kTrainPartial = ((size_t)kParams * 4 + kBiasSums * 8 + 255) / 256 * 256;   // bytes per workgroup
+
+__global__ void __launch_bounds__(256, 1) k_train_block(const float* __restrict__ params,
+                                                        const uint16_t* __restrict__ wb,
+                                                        const uint16_t* __restrict__ X, int n,
+                                                        const float* __restrict__ target, char* __restrict__ partial) {
+    __shared__ __attribute__((aligned(16))) uint16_t w1[128 * kLdw], w2[128 * kLdw], w3[16 * kLdw];
+    __shared__ __attribute__((aligned(16))) uint16_t w2r[128 * kLdw];       // W2 itself, [input][output]
+    __shared__ __attribute__((aligned(16))) float bias[272];
+    // fragments of the workgroup's row groups, [group][tile][lane]
+    __shared__ bf16x4_t frag[3][4][kT][64];
+    auto f_h1 = frag[0], f_d2 = frag[1], f_d1 = frag[2];
+    const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lc = l & 15, lr = 4 * (l >> 4);
+    bf16x4_t x[kT];
+    load_rows(X, blockIdx.x * kRowBlock + wave * 16 + lc, n, l, x);
+    bf16x4_t w3r[kT];                        // W3 rows: hidden unit l % 16 of each tile, outputs lr ..
+#pragma unroll
+    for (int t = 0; t < kT; ++t) w3r[t] = *(const bf16x4_t*)(wb + kW3 + (t * 16 + lc) * FF_LEARN_OUT_PAD + lr);
+    {
+        StagedWeights<128> s1, s2;
+        StagedWeights<16> s3;
+        s1.load(wb + kW1);
+        s2.load(wb + kW2);
+        s3.load(wb + kW3);
+        load_biases(params, bias);
+        s1.store(w1);
+        s2.store(w2);
+        s2.store_rows(w2r);
+        s3.store(w3);
+    }
+    __syncthreads();
+    f32x4_t dw1[2][kT] = {}, dw2[2][kT] = {}, dw3[kT] = {};
+    double db1[kT] = {}, db2[kT] = {}, db3 = 0.0, loss = 0.0;
+    const float inv = 3.0f * (float)n;
+    for (int r0 = blockIdx.x * kRowBlock; r0 < n; r0 += gridDim.x * kRowBlock) {
+        // weights are read again for each row block (kept across the loop they
+        // would fill the registers)
+        asm volatile("" : : : "memory");
+        const int rw = r0 + wave * 16;       // the wavefront's first row
+        // features by rows for dW1, and the targets: used later, loaded now
+        bf16x4_t xr[4][2];
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int row = r0 + g * 16 + lr + q;
+                    const short v = (short)X[(size_t)min(row, n - 1) * FF_LEARN_FEATURES + (2 * wave + u) * 16 + lc];
+                    xr[g][u][q] = row < n ? v : (short)0;
+                }
+        float tg[3], tgr[4];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) tg[c] = target[3 * (size_t)min(rw + lc, n - 1) + c];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) tgr[q] = target[3 * (size_t)min(rw + lr + q, n - 1) + min(lc, 2)];
+        {
+            bf16x4_t h[kT], h2[kT], hr[kT];
+            uint32_t p1, p1r, p2, p2r;
+            hidden_layer<true>(w1, bias, x, l, h, p1, hr, p1r);
+#pragma unroll
+            for (int t = 0; t < kT; ++t) f_h1[wave][t][l] = hr[t];
+            if (r0 + (int)gridDim.x * kRowBlock < n) load_rows(X, rw + lc + gridDim.x * kRowBlock, n, l, x);
+            hidden_layer<true>(w2, bias + 128, h, l, h2, p2, hr, p2r);
+            // output, its error and gradient dY = 2 (Y - T) / (3 n) on the three
+            // used columns, both ways
+            f32x4_t y = {}, yr = {};
+#pragma unroll
+            for (int kt = 0; kt < kT; ++kt) {
+                const bf16x4_t w = weight_frag(w3, 0, kt, l);
+                y = mfma16(w, h2[kt], y);
+                yr = mfma16(h2[kt], w, yr);
+            }
+            f32x4_t dy = {}, dyr = {};
+            if (l < 16 && rw + lc < n)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) dy[c] = 2.0f * (y[c] + bias[256 + c] - tg[c]) / inv;
+            if (lc < 3)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (rw + lr + q < n) {
+                        const float e = yr[q] + bias[256 + lc] - tgr[q];
+                        dyr[q] = 2.0f * e / inv;
+                        loss += (double)(e * e);
+                        db3 += (double)dyr[q];
+                    }
+            const bf16x4_t fdy = pack_bf16(dy), fdyr = pack_bf16(dyr);
+            // dW3 += H2^T dY over the wavefront's rows; dH2 = dY W3^T where H2 > 0
+            bf16x4_t d2[kT];
+#pragma unroll
+            for (int t = 0; t < kT; ++t) {
+                dw3[t] = mfma16(hr[t], fdyr, dw3[t]);
+                f32x4_t a = mfma16(w3r[t], fdy, f32x4_t{}), ar = mfma16(fdy, w3r[t], f32x4_t{});
+                double s = 0.0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    a[q] = (p2 >> (4 * t + q)) & 1u ? a[q] : 0.0f;
+                    ar[q] = (p2r >> (4 * t + q)) & 1u ? ar[q] : 0.0f;
+                    s += (double)ar[q];
+                }
+                db2[t] += s;
+                d2[t] = pack_bf16(a);
+                f_d2[wave][t][l] = pack_bf16(ar);
+            }
+            // dH1 = dH2 W2^T where H1 > 0 (by rows only)
+#pragma unroll
+            for (int t0 = 0; t0 < kT; t0 += 4) {
+                f32x4_t ar[4] = {};
+#pragma unroll
+                for (int kt = 0; kt < kT; ++kt)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) ar[u] = mfma16(d2[kt], weight_frag(w2r, t0 + u, kt, l), ar[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int t = t0 + u;
+                    double s = 0.0;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        ar[u][q] = (p1r >> (4 * t + q)) & 1u ? ar[u][q] : 0.0f;
+                        s += (double)ar[u][q];
+                    }
+                    db1[t] += s;
+                    f_d1[wave][t][l] = pack_bf16(ar[u]);
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const bf16x4_t h1[2] = {f_h1[g][2 * wave][l], f_h1[g][2 * wave + 1][l]};
+#pragma unroll
+            for (int t = 0; t < kT; ++t) {
+                const bf16x4_t d2 = f_d2[g][t][l], d1 = f_d1[g][t][l];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    dw2[u][t] = mfma16(h1[u], d2, dw2[u][t]);
+                    dw1[u][t] = mfma16(xr[g][u], d1, dw1[u][t]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    float* out = (float*)(partial + blockIdx.x * kTrainPartial);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int m = (2 * wave + u) * 16 + lr + q;
+#pragma unroll
+            for (int t = 0; t < kT; ++t) {
+                out[kW1 + m * FF_LEARN_HIDDEN + t * 16 + lc] = dw1[u][t][q];
+                out[kW2 + m * FF_LEARN_HIDDEN + t * 16 + lc] = dw2[u][t][q];
+            }
+        }
+    // dW3: the wavefronts' sums through the fragments' LDS, added in order
+    static_assert(sizeof frag >= 4 * 2048 * 4, "dW3 of four wavefronts");
+    float* s3 = (float*)frag;
+#pragma unroll
+    for (int t = 0; t < kT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s3[wave * 2048 + (t * 16 + lr + q) * FF_LEARN_OUT_PAD + lc] = dw3[t][q];
+    // column sums: over the lanes that share a column, then the wavefronts
+    // (through the weights' LDS, which is no longer needed)
+    double* sums = (double*)w1;
+    auto fold = [&](double v) {
+        v += __shfl_xor(v, 16, 64);
+        return v + __shfl_xor(v, 32, 64);
+    };
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kT; ++t) {
+        const double a = fold(db1[t]), b = fold(db2[t]);
+        if (l < 16) {
+            sums[wave * kBiasSums + t * 16 + l] = a;
+            sums[wave * kBiasSums + 128 + t * 16 + l] = b;
+        }
+    }
+    const double c = fold(db3);
+    double e = fold(loss);
+    e += __shfl_xor(e, 1, 64) + __shfl_xor(e, 2, 64);      // lane 0: columns 0, 1, 2
+    if (l < 16) sums[wave * kBiasSums + 256 + l] = c;
+    if (l == 0) sums[wave * kBiasSums + 272] = e;
+    __syncthreads();
+    for (int k = threadIdx.x; k < 2048; k += 256)
+        out[kW3 + k] = (s3[k] + s3[2048 + k]) + (s3[4096 + k] + s3[6144 + k]);
+    double* dbias = (double*)(out + kParams);
+    static_assert(kParams % 2 == 0, "FP64 partials behind the FP32 ones");
+    for (int k = threadIdx.x; k < kBiasSums; k += 256)
+        dbias[k] = (sums[k] + sums[kBiasSums + k]) + (sums[2 * kBiasSums + k] + sums[3 * kBiasSums + k]);
+}
+
+// Gradient and loss from the workgroups' partial sums, added in FP64 in a fixed
+// order.  A workgroup takes 128 entries: eight groups of 32 threads take four
+// entries each (16-byte loads) of an eighth of the partials; the last
+// workgroup sums the biases and the loss.
+constexpr int kSumEntries = 128;
+static_assert(kB1 % kSumEntries == 0 && kW2 % kSumEntries == 0 && kB2 % kSumEntries == 0 && kW3 % kSumEntries == 0 &&
+              kB3 % kSumEntries == 0, "a workgroup's entries are all weights or all biases");
+__global__ void __launch_bounds__(256) k_gradient_sum(const char* __restrict__ partial, int parts, double loss_scale,
+                                                      float* __restrict__ grad, float* __restrict__ loss) {
+    __shared__ double red[8][kSumEntries];
+    const int t = threadIdx.x, sub = t & 31, grp = t >> 5;
+    const int e0 = blockIdx.x * kSumEntries;
+    const int lo = parts * grp / 8, hi = parts * (grp + 1) / 8;
+    // first bias entry of the workgroup, or -1 for weights
+    const int b0 = e0 == kB1 ? 0 : (e0 == kB2 ? 128 : (e0 == kB3 ? 256 : -1));
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    constexpr int kAhead = 16;               // partials in flight per thread
+    for (int p0 = lo; p0 < hi; p0 += kAhead) {
+        if (b0 < 0) {
+            f32x4_t v[kAhead];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+                v[i] = *(const f32x4_t*)(partial + min(p0 + i, hi - 1) * kTrainPartial + 4 * (size_t)(e0 + 4 * sub));
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s[k] += p0 + i < hi ? (double)v[i][k] : 0.0;
+        } else {
+            double v[kAhead][4];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    v[i][k] = ((const double*)(partial + min(p0 + i, hi - 1) * kTrainPartial +
+                                               kParams * 4))[min(b0 + 4 * sub + k, kBiasSums - 1)];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s[k] += p0 + i < hi ? v[i][k] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[grp][4 * sub + k] = s[k];
+    __syncthreads();
+    if (t >= kSumEntries) return;
+    double v = red[0][t];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) v += red[k][t];
+    if (e0 + t < kParams) grad[e0 + t] = (float)v;
+    else if (e0 + t == kParams) *loss = (float)(loss_scale * v);
+}
+
 // ------------------------------------------------------ loss and backward
 // dY = 2 (Y - T) / (3 n) over the 3 used outputs (zero in the padding), as
 // FP32 and BF16; per-row squared errors for the loss.
@@ -816,16 +1252,15 @@ ff_status lfail(ff_status st, const char* fmt, ...) {
         if (e_ != hipSuccess) return lfail(FF_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
-// parameter offsets (floats) in the packed vector
-constexpr long kW1 = 0, kB1 = kW1 + (long)FF_LEARN_FEATURES * FF_LEARN_HIDDEN;
-constexpr long kW2 = kB1 + FF_LEARN_HIDDEN, kB2 = kW2 + (long)FF_LEARN_HIDDEN * FF_LEARN_HIDDEN;
-constexpr long kW3 = kB2 + FF_LEARN_HIDDEN, kB3 = kW3 + (long)FF_LEARN_HIDDEN * FF_LEARN_OUT_PAD;
-constexpr long kParams = kB3 + FF_LEARN_OUT_PAD;
-
 // activation workspace (bytes) for n rows
 size_t act_bytes(long n) {
     const long h = FF_LEARN_HIDDEN, o = FF_LEARN_OUT_PAD;
     return (size_t)n * (2 * h * 4 + 2 * h * 2 + o * 4) + 256 * 8;
+}
+// The fused network reads features and weights 8 bytes at a time; arrays that
+// are aligned to less take the products one by one.
+bool fused_ok(const uint16_t* features, const uint16_t* params_bf16) {
+    return (uintptr_t)features % 8 == 0 && (uintptr_t)params_bf16 % 8 == 0;
 }
 struct Act {
     float *h1, *h2, *y;
@@ -887,6 +1322,13 @@ ff_status ff_learn_forward(const float* params, const uint16_t* params_bf16, con
     if (workspace_bytes < act_bytes(n_rows) || ((uintptr_t)workspace & 255))
         return lfail(FF_ERR_WORKSPACE, "workspace too small or misaligned");
     hipStream_t st = (hipStream_t)stream;
+    if (fused_ok(features, params_bf16) && (uintptr_t)out % 16 == 0) {
+        const int blocks = (n_rows + kRowBlock - 1) / kRowBlock;
+        hipLaunchKernelGGL(k_forward, dim3(std::min(blocks, kForwardGrid)), dim3(256), 0, st, params, params_bf16,
+                           features, n_rows, out);
+        L_TRY(hipGetLastError());
+        return FF_OK;
+    }
     const Act t = carve(workspace, n_rows);
     const long F = FF_LEARN_FEATURES, H = FF_LEARN_HIDDEN, O = FF_LEARN_OUT_PAD;
     // H1 = relu(X W1 + b1), H2 = relu(H1 W2 + b2), Y = H2 W3 + b3
@@ -906,6 +1348,17 @@ ff_status ff_learn_backward(const float* params, const uint16_t* params_bf16, co
     if (workspace_bytes < need || ((uintptr_t)workspace & 255))
         return lfail(FF_ERR_WORKSPACE, "workspace too small or misaligned (%zu needed)", need);
     hipStream_t st = (hipStream_t)stream;
+    if (fused_ok(features, params_bf16)) {
+        const int parts = std::min((n_rows + kRowBlock - 1) / kRowBlock, kTrainGrid);
+        static_assert(kTrainPartial <= kRowBlock * (2 * 1600), "partial sums fit the workspace");
+        hipLaunchKernelGGL(k_train_block, dim3(parts), dim3(256), 0, st, params, params_bf16, features, n_rows, target,
+                           (char*)workspace);
+        L_TRY(hipGetLastError());
+        hipLaunchKernelGGL(k_gradient_sum, dim3((unsigned)(kParams / kSumEntries + 1)), dim3(256), 0, st, (const char*)workspace,
+                           parts, 1.0 / (3.0 * (double)n_rows), grad, loss);
+        L_TRY(hipGetLastError());
+        return FF_OK;
+    }
     const long F = FF_LEARN_FEATURES, H = FF_LEARN_HIDDEN, O = FF_LEARN_OUT_PAD;
     const long n = n_rows;
     // forward into the first half of the workspace, gradients of the

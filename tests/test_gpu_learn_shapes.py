@@ -52,3 +52,44 @@ def test_features_at_the_edges_of_the_search(sizes, kind):
     fo, nbo = OL.features(x, cat("q"), cat("sigma"), cat("eps"), sa.sys_first_host)
     np.testing.assert_array_equal(nb.cpu().numpy(), nbo)
     np.testing.assert_array_equal(f.cpu().numpy().view(np.uint16), fo)
+
+
+# rows of a wavefront (16) and of a workgroup (64) with remainders, and more
+# row blocks than workgroups of the backward (256) and forward (512) kernels
+@pytest.mark.parametrize("rows", [2, 14, 18, 62, 66, 130])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_network_is_exact_on_exact_inputs_at_row_remainders(rows, shift):
+    """shift = 1: features at an odd 2-byte offset, which the fused kernels'
+    8-byte loads cannot read (the products run one by one)."""
+    from tests.learn_exact import exact_case
+    theta, fbits, T = exact_case(rows, 10 + rows)
+    buf = torch.zeros(fbits.size + shift, dtype=torch.int16, device=DEV)
+    xb = buf[shift:].view(rows, 128)
+    xb.copy_(torch.tensor(fbits.view(np.int16)))
+    net = L.Net(theta, device=DEV)
+    X = OL.bf16_value(fbits)
+    yo, _ = OL.forward(theta.astype(np.float64), X, emulate=True)
+    np.testing.assert_array_equal(net.forward(xb).cpu().numpy().astype(np.float64), yo)
+    loss = net.loss_grad(xb, torch.tensor(T, device=DEV))
+    lo, go = OL.loss_grad(theta.astype(np.float64), X, T.astype(np.float64), emulate=True)
+    assert float(loss.cpu()[0]) == pytest.approx(lo, rel=1e-6)
+    np.testing.assert_array_equal(net.grad.cpu().numpy().astype(np.float64), go)
+
+
+def test_network_over_several_row_blocks_per_workgroup():
+    """Copies of one exact case: 520 row blocks for the forward pass, and 512 for
+    the backward pass, where dY is the small case's times a power of two, so
+    that every product and sum stays exact."""
+    from tests.learn_exact import exact_case
+    theta, fbits, T = exact_case(64, 5)
+    rows = lambda a, k: np.tile(a, (k, 1))  # noqa: E731
+    net = L.Net(theta, device=DEV)
+    y = net.forward(torch.tensor(rows(fbits.view(np.int16), 520), device=DEV)).cpu().numpy().reshape(520, 64, 16)
+    yo, _ = OL.forward(theta.astype(np.float64), OL.bf16_value(fbits), emulate=True)
+    np.testing.assert_array_equal(y.astype(np.float64), np.broadcast_to(yo, y.shape))
+    loss = net.loss_grad(torch.tensor(rows(fbits.view(np.int16), 512), device=DEV),
+                         torch.tensor(rows(T, 512), device=DEV))
+    lo, go = OL.loss_grad(theta.astype(np.float64), OL.bf16_value(rows(fbits, 512)), rows(T, 512).astype(np.float64),
+                          emulate=True)
+    assert float(loss.cpu()[0]) == pytest.approx(lo, rel=1e-6)
+    np.testing.assert_array_equal(net.grad.cpu().numpy(), go.astype(np.float32))
