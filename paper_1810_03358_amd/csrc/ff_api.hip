@@ -3,11 +3,11 @@
 // launch sequence of an evaluation or a minimization.
 //
 // A context holds a batch of independent systems (one or more).  A
-// minimization is a fixed cycle of six kernels captured once into a HIP graph:
-// build the point (trial / direction / momentum) -> bonded terms -> FP32 pair
-// kernel -> FP64 pair kernel -> finalize (+ decision) -> accept pass (+
-// decision).  Each cycle advances every unfinished system by one evaluation;
-// work of a system that has nothing to do in a kernel returns at once (its
+// minimization is a fixed cycle of kernels captured once into a HIP graph:
+// build the point (trial / direction / momentum) -> FP32 pair kernel -> FP64
+// pair kernel (each with the bonded terms of the systems that it evaluates) ->
+// finalize (+ decision) -> accept pass (+ decision).  Each cycle advances every
+// unfinished system by one evaluation; work of a system that has nothing to do in a kernel returns at once (its
 // control block says so).  The host replays the graph and polls the number of
 // finished systems.
 #include <algorithm>
@@ -26,7 +26,6 @@
 
 namespace ff {
 hipError_t launch_pair(const Args& a, int prec, hipStream_t s);
-hipError_t launch_bonded(const Args& a, hipStream_t s);
 hipError_t launch_finalize(const Args& a, hipStream_t s);
 hipError_t launch_cycle_vec(const Args& a, int which, hipStream_t s);
 hipError_t launch_profile_point(const Args& a, const double* x, const double* g, const double* g2, double t,
@@ -141,6 +140,17 @@ static RowSplit row_split(int T, int c) {
     return r;
 }
 
+// Chunk length of the FP64 table in parts: `chunk` j-tiles; where one-tile
+// chunks would be fewer wavefronts than half the SIMDs, a half or a quarter of
+// a tile (FP64 evaluation of 1,500 atoms: 19.6 us with 4 parts, 21.7 with 8;
+// 512 atoms: 16.6 with 2, 21.0 with 8, 17.2 with 1).
+static int fp64_split(int chunk, long long units, int waves) {
+    int split = chunk * kParts;
+    if (chunk == 1)
+        while (split > 2 && units * waves * (kParts / split) < 512) split /= 2;
+    return split;
+}
+
 static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout& L, SysInfo* sys, FarTmp& ft,
                         int32_t cfg_req = -1, int32_t chunk_req = 0, int32_t chunk64_req = 0,
                         bool energy_only = false) {
@@ -157,30 +167,27 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
     if (n_tot > (1 << 28)) return false;
     if (ft.cap < far_capacity(s, n_sys)) return false;
     L.n_sys = n_sys;
-    // defaults from sweeps of whole FP32 and FP64 evaluations on MI355X
-    // (2,048 to 50,000 atoms, configurations x chunk lengths 1 to 16, per
-    // precision): batches use 128-atom blocks with two atoms per lane in both
-    // kernels (the 256-chain batch of 200-4,000 atoms: 4 % less per FP64
-    // evaluation than with 64-atom blocks, 2 % more per FP32 one); systems up
-    // to 1,024 atoms 64-atom blocks; up to 12,288 atoms 256-atom blocks with
-    // one atom per lane (enough workgroups to fill the chip); up to 20,000
-    // atoms 128-atom blocks with two atoms per lane (15k atoms: 5 % less per
-    // evaluation than 256-atom blocks); above, 256-atom blocks with two atoms
-    // per lane in FP32 and four in FP64.  The FP64 kernel, with fewer and
-    // longer-lived wavefronts, gains from longer chunks as the system grows
-    // (two j-tiles from 6,145 atoms up to 12,287 and from 20,000, four from
-    // 32,768, eight from 45,000 on: 1.49 instead of 1.55 ms per FP64
-    // evaluation at 50k atoms), the FP32 kernel from two j-tiles only above
-    // 32,768 atoms
+    // defaults from sweeps of whole FP32 and FP64 evaluations on MI355X (300 to
+    // 50,000 atoms and batches, configurations x chunk lengths, per precision).
+    // Blocks: 64 atoms up to 1,024; 256 with one atom per lane up to 12,288
+    // (enough workgroups to fill the chip); 128 with two up to 20,000 and in
+    // batches, whose small systems larger blocks would pad; 256 with two atoms
+    // per lane in FP32 and four in FP64 above.  The FP64 chunks grow with the
+    // system: one j-tile up to 14,500 (13,000 atoms: 127.0 us, 133.4 with two),
+    // two up to 40,000 (30,000 atoms: 534 us, 558 with one, 536 with four), four
+    // above (50,000 atoms: 1,397 us, 1,428 with two, 1,437 with eight); batches
+    // one (96 chains of 200-4,000 atoms: 208.8 us, 215.5 with four).  The FP32
+    // kernel gains from two j-tiles only above 32,768 atoms, and from four in
+    // batches.
     auto pick = [&](int cfg, int c32, int c64) { L.cfg = cfg; L.chunk[0] = c32; L.chunk[1] = c64; };
-    if (n_sys > 1) pick(9, 4, 4);
+    if (n_sys > 1) pick(9, 4, 1);
     else if (n_max <= 1024) pick(0, 1, 1);
-    else if (n_max <= 6144) pick(1, 1, 1);
-    else if (n_max < 12288) pick(1, 1, 2);
-    else if (n_max < 20000) pick(9, 1, 1);
+    else if (n_max < 12288) pick(1, 1, 1);
+    else if (n_max <= 14500) pick(9, 1, 1);
+    else if (n_max < 20000) pick(9, 1, 2);
     else if (n_max < 32768) pick(8, 1, 2);
-    else if (n_max < 45000) pick(8, 2, 4);
-    else pick(8, 2, 8);
+    else if (n_max <= 40000) pick(8, 2, 2);
+    else pick(8, 2, 4);
     if (cfg_req >= 0) {
         if (chunk64_req == 0) chunk64_req = chunk_req;
         if (cfg_req >= kNumTileConfigs || chunk_req < 1 || chunk_req > kMaxChunk || chunk64_req < 1 ||
@@ -189,6 +196,12 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
         pick(cfg_req, chunk_req, chunk64_req);
     }
     L.block = kTileConfigs[L.cfg].block;
+    long long n_units = 0;
+    for (int k = 0; k < n_sys; ++k) {
+        const long long nb = (s[k].n_atoms + L.block - 1) / L.block;
+        n_units += nb * (nb + 1) / 2 * (L.block / kTile);
+    }
+    L.split = fp64_split(L.chunk[1], n_units, kTileConfigs[L.cfg].waves64);
     int aoff = 0, uoff = 0, units = 0, nbd = 0, nag = 0, ndh = 0, ebo = 0;
     int chunks[2] = {0, 0};
     size_t red = 0;
@@ -208,7 +221,8 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
         for (int b = 0; b < si.nb; ++b) {
             const int t0 = b * L.block / kTile;
             units += nt - t0;
-            for (int p = 0; p < 2; ++p) chunks[p] += row_split(nt - t0, L.chunk[p]).count();
+            chunks[0] += row_split(nt - t0, L.chunk[0]).count();
+            chunks[1] += ((nt - t0) * kParts + L.split - 1) / L.split;
         }
         for (int p = 0; p < 2; ++p) si.n_chunks[p] = chunks[p] - si.chunk0[p];
         si.n_bonds = s[k].n_bonds;
@@ -293,7 +307,7 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
     L.off_batch = take(sizeof(BatchState));
     L.off_ctl = take((size_t)n_sys * L.ctl_stride);
     L.off_pi = take(max_chunks * L.block * 3 * 8);
-    L.off_pj = take((size_t)L.n_units * kTile * 3 * 8);
+    L.off_pj = take((size_t)L.n_units * unit_rows(L.split) * kTile * 3 * 8);
     L.off_ep = take(max_chunks * 8);
     L.off_fb = take((size_t)L.n_terms_slots * 24);
     L.off_eb = take((size_t)L.n_bonded_blocks * 8);
@@ -416,23 +430,24 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
         const SysInfo& si = sys[k];
         const int tile0 = si.aoff / kTile, nt = si.np / kTile;
         for (int b = 0; b < si.nb; ++b) {
-            const int row = si.row0 + b;
-            const int t0 = tile0 + b * L.block / kTile, t_end = tile0 + nt;
-            rows[row].unit_start = unit;
-            rows[row].t0 = t0;
-            for (int p = 0; p < 2; ++p) {
-                rows[row].chunk_start[p] = slot[p];
-                rows[row].n_chunks[p] = row_split(t_end - t0, L.chunk[p]).count();
-                slot[p] += rows[row].n_chunks[p];
-            }
-            unit += t_end - t0;
+            RowInfo& r = rows[si.row0 + b];
+            r.t0 = tile0 + b * L.block / kTile;
+            const int T = tile0 + nt - r.t0;
+            r.unit_start = unit;
+            r.chunk_start[0] = slot[0];
+            r.chunk_start[1] = slot[1];
+            r.n_chunks[0] = row_split(T, L.chunk[0]).count();
+            r.n_chunks[1] = (T * kParts + L.split - 1) / L.split;
+            slot[0] += r.n_chunks[0];
+            slot[1] += r.n_chunks[1];
+            unit += T;
         }
     }
     if (slot[0] != L.n_chunks[0] || slot[1] != L.n_chunks[1] || unit != L.n_units)
         return fail(FF_ERR_ARG, "internal: tile table size mismatch");
-    for (int p = 0; p < 2; ++p) {
-        ChunkInfo* chunks = at<ChunkInfo>(img, L.off_chunks[p]);
-        const int c_len = L.chunk[p];
+    {
+        ChunkInfo* chunks = at<ChunkInfo>(img, L.off_chunks[0]);
+        const int c_len = L.chunk[0];
         int nch = 0;
         for (int pass = 0; pass < 3; ++pass) {
             for (int k = 0; k < n_sys; ++k) {
@@ -441,16 +456,17 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
                 for (int row = si.row0; row < si.row0 + si.nb; ++row) {
                     const RowInfo& ri = rows[row];
                     const RowSplit sp = row_split(t_end - ri.t0, c_len);
-                    int t = ri.t0, q = ri.chunk_start[p];
+                    int t = ri.t0, q = ri.chunk_start[0];
                     auto emit = [&](int len, int in_pass) {
                         if (in_pass == pass) {
                             ChunkInfo& c = chunks[nch++];
                             c.row = row;
                             c.t_begin = t;
                             c.t_end = t + len;
-                            c.unit_base = ri.unit_start + (t - ri.t0);
+                            c.j_row = c.unit = ri.unit_start + (t - ri.t0);
                             c.sys = k;
                             c.slot = q;
+                            c.steps = kTile << 8;
                         }
                         t += len;
                         ++q;
@@ -458,12 +474,41 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
                     for (int i = 0; i < sp.full; ++i) emit(c_len, c_len == 1 ? 2 : 0);
                     if (sp.rem > 0) emit(sp.rem, sp.rem == 1 ? 2 : 1);
                     for (int i = 0; i < sp.tail; ++i) emit(1, 2);
-                    if (t != t_end || q != ri.chunk_start[p] + ri.n_chunks[p])
+                    if (t != t_end || q != ri.chunk_start[0] + ri.n_chunks[0])
                         return fail(FF_ERR_ARG, "internal: chunk split mismatch");
                 }
             }
         }
-        if (nch != L.n_chunks[p]) return fail(FF_ERR_ARG, "internal: chunk table size mismatch");
+        if (nch != L.n_chunks[0]) return fail(FF_ERR_ARG, "internal: chunk table size mismatch");
+    }
+    {
+        // FP64: full-length chunks first, then each I-block's shorter last one
+        ChunkInfo* chunks = at<ChunkInfo>(img, L.off_chunks[1]);
+        int nch = 0;
+        for (int pass = 0; pass < 2; ++pass)
+            for (int k = 0; k < n_sys; ++k) {
+                const SysInfo& si = sys[k];
+                const int t_end = si.aoff / kTile + si.np / kTile;
+                for (int row = si.row0; row < si.row0 + si.nb; ++row) {
+                    const RowInfo& ri = rows[row];
+                    const int parts = (t_end - ri.t0) * kParts;
+                    for (int c = 0; c < ri.n_chunks[1]; ++c) {
+                        const int e0 = c * L.split, e1 = std::min(parts, e0 + L.split);
+                        if ((e1 - e0 == L.split) != (pass == 0)) continue;
+                        ChunkInfo& o = chunks[nch++];
+                        const int k0 = e0 / kParts, k1 = (e1 - 1) / kParts;
+                        o.row = row;
+                        o.t_begin = ri.t0 + k0;
+                        o.t_end = ri.t0 + k1 + 1;
+                        o.unit = ri.unit_start + k0;
+                        o.j_row = o.unit * unit_rows(L.split) + (L.split < kParts ? c % unit_rows(L.split) : 0);
+                        o.sys = k;
+                        o.slot = ri.chunk_start[1] + c;
+                        o.steps = (e0 - k0 * kParts) * kPartSteps | (e1 - k1 * kParts) * kPartSteps << 8;
+                    }
+                }
+            }
+        if (nch != L.n_chunks[1]) return fail(FF_ERR_ARG, "internal: chunk table size mismatch");
     }
     // bonded topology (local atom indices) and parameters
     int* bond = at<int>(img, L.off_bond);
@@ -550,7 +595,7 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
     return FF_OK;
 }
 
-// Bonded terms, pair kernel and finalize of one direct evaluation.
+// Pair kernel (with the bonded terms) and finalize of one direct evaluation.
 static ff_status launch_energy(const Layout& L, char* ws, const double* xyz, double* energy, double* grad,
                                int32_t precision, hipStream_t st) {
     Args a{};
@@ -560,8 +605,8 @@ static ff_status launch_energy(const Layout& L, char* ws, const double* xyz, dou
     a.e_out = energy;
     a.g_out = grad;
     a.direct = 1;
+    a.bonded = 1;
     a.direct_prec = precision;
-    HIP_TRY(launch_bonded(a, st));
     HIP_TRY(launch_pair(a, precision, st));
     HIP_TRY(launch_finalize(a, st));
     return FF_OK;
@@ -866,13 +911,13 @@ static ff_status build_graph(ff_ctx* c, bool with32, hipGraphExec_t* out) {
     Args a{};
     a.L = c->L;
     a.ws = c->ws;
+    a.bonded = 1;
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
     // several cycles per graph: each graph launch costs a few us of its own
     hipError_t e = hipSuccess;
     for (int k = 0; k < kCyclesPerGraph && e == hipSuccess; ++k) {
         e = launch_cycle_vec(a, 0, st);
-        if (e == hipSuccess) e = launch_bonded(a, st);
         if (e == hipSuccess && with32) e = launch_pair(a, 1, st);
         if (e == hipSuccess) e = launch_pair(a, 0, st);
         if (e == hipSuccess) e = launch_finalize(a, st);
@@ -1020,12 +1065,12 @@ ff_status ff_energy_profile(ff_ctx* c, const double* xyz, const double* t, int32
     a.L = L;
     a.ws = c->ws;
     a.direct = 1;
+    a.bonded = 1;
     a.direct_prec = precision;
     a.xyz_in = xyz;
     a.e_out = e;                 // scratch for E(x) itself
     a.g_out = g;
     a.g2_out = g2;
-    HIP_TRY(launch_bonded(a, st));
     HIP_TRY(launch_pair(a, precision, st));
     HIP_TRY(launch_finalize(a, st));
     a.xyz_in = xt;
@@ -1034,7 +1079,6 @@ ff_status ff_energy_profile(ff_ctx* c, const double* xyz, const double* t, int32
     for (int k = 0; k < n_t; ++k) {
         a.e_out = e + (size_t)(k + 1) * L.n_sys;
         HIP_TRY(launch_profile_point(a, xyz, g, g2, t[k], xt, st));
-        HIP_TRY(launch_bonded(a, st));
         HIP_TRY(launch_pair(a, precision, st));
         HIP_TRY(launch_finalize(a, st));
     }

@@ -24,7 +24,7 @@ constexpr int kMaxM = 32;            // largest L-BFGS memory
 constexpr int kNumSlots = 8;         // point slots (x and grad) of the optimizer
 constexpr int kMaxTerms = 2 * kMaxM + 2;   // linear-combination terms of a direction
 constexpr int kGramDim = 2 * kMaxM + 1;    // Gram matrix over {s_i, y_i, g}
-constexpr int kFinBlock = 256;       // threads of the finalize / vector kernels
+constexpr int kFinBlock = 256;       // threads of the vector and reduce kernels
 constexpr int kMaxDots = 6 * kMaxM + 8;    // dot products per vector pass
 constexpr int kMaxLsTrials = 8;
 constexpr int kBondedPerBlock = 256;  // bonded terms per workgroup
@@ -174,21 +174,30 @@ constexpr TileConfig kTileConfigs[] = {
 constexpr int kNumTileConfigs = sizeof(kTileConfigs) / sizeof(kTileConfigs[0]);
 
 // ------------------------------------------------------------- tile tables
-// The chunk table is in launch order: every chunk of the full length first,
+// FP32 chunk table, in launch order: every chunk of the full length first,
 // then the shorter ones, so that the last workgroups of a launch are the
 // shortest.  With chunks longer than one j-tile, the last 1/kTailDiv of each
 // I-block's j-tiles (at least one) go to one-tile chunks, which end the
 // launch.  A chunk's `slot` numbers it within its I-block in j order (the
 // I-block's chunks hold consecutive slots): the slot indexes its i-side
 // partial row and its energy share.
+//
+// FP64 chunk table: each I-block's j range is cut into equal runs of
+// Layout::split parts (the last one shorter), a part being kPartSteps of the 64
+// steps of a j-tile: whole tiles (a multiple of kParts), or 1, 2 or 4 parts where
+// a system's tiles are too few to fill the chip.  Chunks shorter than a tile
+// have a j-side row each, kParts / split of them for every unit.
 constexpr int kTailDiv = 16;
+constexpr int kPartSteps = 8;
+constexpr int kParts = kTile / kPartSteps;     // parts of a j-tile
 struct ChunkInfo {        // one workgroup of the pair kernel
     int32_t row;          // I-block index (global)
     int32_t t_begin, t_end;   // j-tiles [t_begin, t_end) (global)
-    int32_t unit_base;    // index of unit (row, t_begin) in the Fj partial array
+    int32_t j_row;        // j-side partial row of t_begin
     int32_t sys;          // system the chunk belongs to
     int32_t slot;         // i-side partial row and energy share of the chunk
-    int32_t pad_[2];
+    int32_t unit;         // unit (row, t_begin): far-exclusion lookups
+    int32_t steps;        // first step in t_begin | end step in t_end - 1 << 8
 };
 struct RowInfo {          // one I-block
     int32_t unit_start;   // unit index of (row, t0)
@@ -196,6 +205,8 @@ struct RowInfo {          // one I-block
     int32_t chunk_start[2];   // slot of its first chunk, per chunk table
     int32_t n_chunks[2];
 };
+// j-side rows of a unit in the FP64 table.
+__host__ __device__ inline int unit_rows(int split) { return split < kParts ? kParts / split : 1; }
 
 // One system of a batch.  Atom indices in its topology are local (0..n-1);
 // "global" indices count padded atoms over the whole batch.
@@ -219,6 +230,7 @@ struct Layout {
     int32_t n, np, nb, nt, block, n_units;   // n, np: totals over the batch
     int32_t chunk[2], n_chunks[2];        // chunk length and chunks: [0] FP32 kernel, [1] FP64 kernel
     int32_t n_bonds, n_angles, n_dihedrals, n_terms_slots, n_bonded_blocks;
+    int32_t split;            // FP64 chunk length in parts
     int32_t n_far_units;      // units holding an excluded pair more than kExclWindow apart
     int32_t n_fin_blocks;
     // flat grids: workgroup b of a pass handles (system, local block) = map[b]
@@ -252,6 +264,7 @@ struct Args {
     double* g_out;           // direct mode: gradient [sum n][3] or null
     double* g2_out;          // direct mode: |grad E|^2 per system, or null
     int32_t direct;          // 1: ff_energy_grad, 0: optimizer cycle
+    int32_t bonded;          // the pair kernel also evaluates the bonded terms
     int32_t direct_prec;
 };
 
@@ -267,6 +280,19 @@ __host__ __device__ inline SysInfo* sys_info(const Args& a) { return at<SysInfo>
 
 __host__ __device__ inline Ctl* ctl_at(const Args& a, int sys) {
     return reinterpret_cast<Ctl*>(a.ws + a.L.off_ctl + (size_t)sys * a.L.ctl_stride);
+}
+
+// Does system `sys` evaluate in precision `prec` this cycle?
+__device__ __forceinline__ bool eval_active(const Args& a, int sys, int prec) {
+    if (a.direct) return a.direct_prec == prec;
+    const Ctl* c = ctl_at(a, sys);
+    return c->action == ACT_EVAL && c->prec == prec && c->target >= 0 && c->target < kNumSlots;
+}
+
+// Coordinates of system `si` for this evaluation ([n][3], local atom index).
+__device__ __forceinline__ const double* eval_coords(const Args& a, int sys, const SysInfo& si) {
+    if (a.direct) return a.xyz_in + 3 * (size_t)si.uoff;
+    return vec(a, V_X0 + ctl_at(a, sys)->target, si);
 }
 
 // Coordinates of padding atoms (index >= n): far away, mutually separated,

@@ -151,17 +151,24 @@ __device__ void lbfgs_direction_block(Ctl* c) {
 }
 
 // ------------------------------------------------------------------ finalize
+// Partial rows in flight per wavefront of k_finalize, which is bound by their
+// latency (10,000 atoms, FP32 rows: 10.5 us with eight, 12.1 with four; 16 are
+// no faster, and slower in batches: 28 us against 22 for 96 chains of 4,000).
+constexpr int kFlight = 8;
+constexpr int kSlots = 3;        // bonded-term slots a thread fetches at a time
+
 // Pair partials of one 64-atom tile t of I-block `row`, summed over its
 // partial rows in a fixed order.  The tile's rows are the i-side partials
 // of every chunk of its I-block, then the j-side partials of every unit that
-// holds tile t (I-blocks row0..row).  Each row is 192 contiguous values
+// holds tile t (I-blocks row0..row; in the FP64 table a unit whose tile is cut
+// into parts has a row for each).  Each row is 192 contiguous values
 // (64 atoms x xyz); wavefront w of the workgroup sums rows w, w+4, ... (lane
 // l holds values l, l+64, l+128), the four wavefront sums are then added in
 // order.  T is the storage type of the partials (FP32 mode: float).
 template <typename T>
 __device__ __forceinline__ void gather_tile(const Args& a, const SysInfo& si, int row, int t,
-                                            double* tot /* LDS [192] */) {
-    __shared__ double part[kFinBlock / 64][3 * kTile];
+                                            double* tot /* LDS [192] */, double (*part)[3 * kTile] /* LDS */) {
+    constexpr int kWaves = kFinBlock / 64;
     const Layout& L = a.L;
     const RowInfo* R = at<RowInfo>(a.ws, L.off_rows);
     const T* Pi = at<T>(a.ws, L.off_pi);
@@ -170,9 +177,9 @@ __device__ __forceinline__ void gather_tile(const Args& a, const SysInfo& si, in
     const RowInfo ri = R[row];
     const int il0 = t * kTile - row * L.block;
     constexpr int tab = sizeof(T) == 4 ? 0 : 1;          // chunk table of the kernel that wrote Pi
-    const int n_i = ri.n_chunks[tab], nseg = n_i + row - row0 + 1;
+    const int per = tab == 0 ? 1 : unit_rows(L.split);   // rows of a unit
+    const int n_i = ri.n_chunks[tab], nseg = n_i + (row - row0 + 1) * per;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    constexpr int kWaves = kFinBlock / 64;
     // Units of a system are numbered row by row, local row r holding tiles
     // r*B/64 .. nt-1, so the unit of (row r, tile tl) has a closed form and
     // the addresses need no table loads.
@@ -181,41 +188,58 @@ __device__ __forceinline__ void gather_tile(const Args& a, const SysInfo& si, in
     const long long tl = t - si.aoff / kTile;
     auto seg = [&](int sg) -> const T* {
         if (sg < n_i) return Pi + ((size_t)(ri.chunk_start[tab] + sg) * L.block + il0) * 3;
-        const long long r = sg - n_i;
+        const int q = sg - n_i;
+        const long long r = per == 1 ? q : q / per;
         const long long unit = u0 + r * nt - b64 * r * (r - 1) / 2 + (tl - r * b64);
-        return Pj + (size_t)unit * (3 * kTile);
+        return Pj + (size_t)(per == 1 ? unit : unit * per + (q - r * per)) * (3 * kTile);
     };
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    int sg = wave;
-    // four rows in flight per wavefront, added in row order
-    for (; sg + 3 * kWaves < nseg; sg += 4 * kWaves) {
-        const T* p0 = seg(sg);
-        const T* p1 = seg(sg + kWaves);
-        const T* p2 = seg(sg + 2 * kWaves);
-        const T* p3 = seg(sg + 3 * kWaves);
-        const T v00 = p0[lane], v01 = p0[lane + 64], v02 = p0[lane + 128];
-        const T v10 = p1[lane], v11 = p1[lane + 64], v12 = p1[lane + 128];
-        const T v20 = p2[lane], v21 = p2[lane + 64], v22 = p2[lane + 128];
-        const T v30 = p3[lane], v31 = p3[lane + 64], v32 = p3[lane + 128];
-        a0 += (double)v00; a1 += (double)v01; a2 += (double)v02;
-        a0 += (double)v10; a1 += (double)v11; a2 += (double)v12;
-        a0 += (double)v20; a1 += (double)v21; a2 += (double)v22;
-        a0 += (double)v30; a1 += (double)v31; a2 += (double)v32;
+    double acc[3] = {};
+    // kFlight rows in flight per wavefront, added in row order; past the last
+    // row nothing is added (0.0 to a sum that began at 0.0)
+    for (int sg = wave; sg < nseg; sg += kFlight * kWaves) {
+        T v[kFlight][3];
+#pragma unroll
+        for (int f = 0; f < kFlight; ++f) {
+            const T* p = seg(min(sg + f * kWaves, nseg - 1)) + lane;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) v[f][k] = p[64 * k];
+        }
+#pragma unroll
+        for (int f = 0; f < kFlight; ++f)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) acc[k] += sg + f * kWaves < nseg ? (double)v[f][k] : 0.0;
     }
-    for (; sg < nseg; sg += kWaves) {
-        const T* p0 = seg(sg);
-        a0 += (double)p0[lane]; a1 += (double)p0[lane + 64]; a2 += (double)p0[lane + 128];
-    }
-    part[wave][lane] = a0;
-    part[wave][lane + 64] = a1;
-    part[wave][lane + 128] = a2;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) part[wave][lane + 64 * k] = acc[k];
     __syncthreads();
     if (threadIdx.x < 3 * kTile) {
         double v = part[0][threadIdx.x];
+#pragma unroll
         for (int w = 1; w < kWaves; ++w) v += part[w][threadIdx.x];
         tot[threadIdx.x] = v;
     }
     __syncthreads();
+}
+
+// floor(count * b / nb) for b <= nb (a 64-bit division costs 150 instructions).
+__device__ __forceinline__ int share_begin(int count, int b, int nb) {
+    const unsigned q = (unsigned)count / (unsigned)nb, r = (unsigned)count % (unsigned)nb;
+    const unsigned rest = nb < 65536 ? r * (unsigned)b / (unsigned)nb : (unsigned)((unsigned long long)r * b / nb);
+    return (int)(q * (unsigned)b + rest);
+}
+
+// Share of tile `blk` in the energies of a system's pair chunks (table `tab`)
+// and bonded blocks, per thread.
+__device__ __forceinline__ double energy_share(const Args& a, const SysInfo& si, int blk, int tab) {
+    const double* ep = at<double>(a.ws, a.L.off_ep) + si.chunk0[tab];
+    const double* eb = at<double>(a.ws, a.L.off_eb) + si.eb0;
+    const int nb = si.fin_blocks, nc = si.n_chunks[tab];
+    const int p0 = share_begin(nc, blk, nb), p1 = share_begin(nc, blk + 1, nb);
+    const int q0 = share_begin(si.bonded_blocks, blk, nb), q1 = share_begin(si.bonded_blocks, blk + 1, nb);
+    double e = 0.0;
+    for (int k = p0 + (int)threadIdx.x; k < p1; k += kFinBlock) e += ep[k];
+    for (int k = q0 + (int)threadIdx.x; k < q1; k += kFinBlock) e += eb[k];
+    return e;
 }
 
 // One workgroup per 64-atom tile of a system: gradient = pair partials of
@@ -236,10 +260,9 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(Args a) {
     const int t = si.aoff / kTile + blk;                 // global tile
     const int row = t * kTile / L.block;                 // its I-block
     __shared__ double tot[3 * kTile];
-    __shared__ double fbv[kFinBlock][3];
+    __shared__ double part[kFinBlock / 64][3 * kTile];
+    __shared__ double fbv[kSlots * kFinBlock][3];
     const bool p32 = a.direct ? a.direct_prec == 1 : c->prec == 1;
-    if (p32) gather_tile<float>(a, si, row, t, tot);
-    else gather_tile<double>(a, si, row, t, tot);
     // bonded-term slots of the tile's atoms: contiguous in the incidence list
     const int* inc0 = at<int>(a.ws, L.off_inc_start);
     const int* inc = at<int>(a.ws, L.off_inc);
@@ -247,26 +270,41 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(Args a) {
     const int ga = t * kTile + (int)threadIdx.x;         // global padded atom (threads < 64)
     const int k_lo = inc0[t * kTile], k_hi = inc0[t * kTile + kTile];
     int my_lo = 0, my_hi = 0;
-    double gx = 0.0, gy = 0.0, gz = 0.0;
     if (threadIdx.x < kTile) {
         my_lo = inc0[ga];
         my_hi = inc0[ga + 1];
+    }
+    // kSlots slots of a thread from `base` (past the last slot its values again,
+    // which nothing reads); the first ones are on their way while the partial
+    // rows are summed
+    double fb[kSlots][3];
+    auto fetch = [&](int base) {
+#pragma unroll
+        for (int m = 0; m < kSlots; ++m) {
+            const double* p = FB + 3 * (size_t)inc[min(base + m * kFinBlock + (int)threadIdx.x, k_hi - 1)];
+            fb[m][0] = p[0]; fb[m][1] = p[1]; fb[m][2] = p[2];
+        }
+    };
+    if (k_lo < k_hi) fetch(k_lo);
+    double e = energy_share(a, si, blk, p32 ? 0 : 1);
+    if (p32) gather_tile<float>(a, si, row, t, tot, part);
+    else gather_tile<double>(a, si, row, t, tot, part);
+    double gx = 0.0, gy = 0.0, gz = 0.0;
+    if (threadIdx.x < kTile) {
         gx = tot[3 * threadIdx.x];
         gy = tot[3 * threadIdx.x + 1];
         gz = tot[3 * threadIdx.x + 2];
     }
-    for (int base = k_lo; base < k_hi; base += kFinBlock) {
-        const int k = base + (int)threadIdx.x;
-        if (k < k_hi) {
-            const double* p = FB + 3 * (size_t)inc[k];
-            fbv[threadIdx.x][0] = p[0];
-            fbv[threadIdx.x][1] = p[1];
-            fbv[threadIdx.x][2] = p[2];
-        }
+    for (int base = k_lo; base < k_hi; base += kSlots * kFinBlock) {
+        if (base > k_lo) fetch(base);
+#pragma unroll
+        for (int m = 0; m < kSlots; ++m)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) fbv[m * kFinBlock + (int)threadIdx.x][q] = fb[m][q];
         __syncthreads();
         if (threadIdx.x < kTile) {
-            const int e = min(my_hi, base + kFinBlock);
-            for (int q = max(my_lo, base); q < e; ++q) {
+            const int end = min(my_hi, base + kSlots * kFinBlock);
+            for (int q = max(my_lo, base); q < end; ++q) {
                 gx += fbv[q - base][0]; gy += fbv[q - base][1]; gz += fbv[q - base][2];
             }
         }
@@ -279,28 +317,15 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(Args a) {
     double v[4];
     v[0] = fmax(fabs(gx), fmax(fabs(gy), fabs(gz)));
     if (isnan(gx) || isnan(gy) || isnan(gz)) v[0] = __builtin_inf();
-    v[1] = gx * gx + gy * gy + gz * gz;
+    v[1] = fma(gz, gz, fma(gy, gy, gx * gx));
     v[2] = 0.0;
     if (want_slope && real) {
         const double* gb = vec(a, V_G0 + c->slope_slot, si);
         const double* d = vec(a, V_D, si);
         const size_t o = 3 * (size_t)atom;
-        v[2] = gb[o] * d[o] + gb[o + 1] * d[o + 1] + gb[o + 2] * d[o + 2];
+        v[2] = fma(gb[o + 2], d[o + 2], fma(gb[o], d[o], gb[o + 1] * d[o + 1]));
     }
-    // this workgroup's share of the pair-workgroup and bonded-block energies
-    {
-        const int nb = si.fin_blocks, b = blk;
-        const int tab = p32 ? 0 : 1;                     // chunk table of the pair kernel that ran
-        const double* ep = at<double>(a.ws, L.off_ep) + si.chunk0[tab];
-        const double* eb = at<double>(a.ws, L.off_eb) + si.eb0;
-        const int nc = si.n_chunks[tab];
-        const int p0 = (int)((long long)nc * b / nb), p1 = (int)((long long)nc * (b + 1) / nb);
-        const int q0 = (int)((long long)si.bonded_blocks * b / nb), q1 = (int)((long long)si.bonded_blocks * (b + 1) / nb);
-        double e = 0.0;
-        for (int k = p0 + (int)threadIdx.x; k < p1; k += kFinBlock) e += ep[k];
-        for (int k = q0 + (int)threadIdx.x; k < q1; k += kFinBlock) e += eb[k];
-        v[3] = e;
-    }
+    v[3] = e;
     double* red = at<double>(a.ws, L.off_red) + si.red0;
     double tr[4];
     block_reduce<4>(v, true, tr);

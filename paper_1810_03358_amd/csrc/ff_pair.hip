@@ -5,8 +5,9 @@
 // Work decomposition.  Atoms are padded to np (multiple of 512) with
 // zero-parameter atoms placed far away.  The upper triangle of the pair
 // matrix is cut into units (I-block of B atoms) x (j-tile of 64 atoms), j-tile
-// index t >= B*row/64; a workgroup ("chunk") walks a run of j-tiles of one
-// I-block.  Each lane keeps IPL i-atoms in registers; the j-tile sits in LDS
+// index t >= B*row/64; a chunk (a workgroup, or one of a workgroup's wavefronts)
+// walks a run of j-tiles of one I-block, or in small FP64 systems a part of a
+// tile.  Each lane keeps IPL i-atoms in registers; the j-tile sits in LDS
 // twice in a row so that at step s lane l reads entry l+s (atom (l+s) mod 64)
 // with an immediate offset.  The gradient on j is accumulated in a register
 // that moves one lane down after every step (DPP wave rotation), so after 64
@@ -56,19 +57,6 @@ __device__ __forceinline__ double rotate_down(double v) {
     const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffLL), FF_DPP_ROTATE, 0xF, 0xF, false);
     const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), FF_DPP_ROTATE, 0xF, 0xF, false);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Does system `sys` evaluate in precision `prec` this cycle?
-__device__ __forceinline__ bool eval_active(const Args& a, int sys, int prec) {
-    if (a.direct) return a.direct_prec == prec;
-    const Ctl* c = ctl_at(a, sys);
-    return c->action == ACT_EVAL && c->prec == prec && c->target >= 0 && c->target < kNumSlots;
-}
-
-// Coordinates of system `si` for this evaluation ([n][3], local atom index).
-__device__ __forceinline__ const double* eval_coords(const Args& a, int sys, const SysInfo& si) {
-    if (a.direct) return a.xyz_in + 3 * (size_t)si.uoff;
-    return vec(a, V_X0 + ctl_at(a, sys)->target, si);
 }
 
 __device__ __forceinline__ void load_pos(const double* X, int32_t atom, int32_t n, double* p) {
@@ -178,29 +166,54 @@ __device__ double bonded_term(const Args& a, const double* X, const SysInfo& si,
     return e;
 }
 
-__device__ void bonded_block(const Args& a, const double* X, const SysInfo& si, int blk, int nthreads) {
-    double e = 0.0;
-    const int first = blk * kBondedPerBlock;
-    for (int t = first + (int)threadIdx.x; t < first + kBondedPerBlock; t += nthreads) e += bonded_term(a, X, si, t);
-    // deterministic block sum of the term energies
-    __shared__ double red[kBondedPerBlock];
-    red[threadIdx.x] = e;
-    __syncthreads();
-    for (int s = nthreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) at<double>(a.ws, a.L.off_eb)[si.eb0 + blk] = red[0];
+// Pairwise sum of v[0 .. N): halves are added, then quarters, and so on.
+template <int N>
+__device__ __forceinline__ double tree_sum(double (&v)[N]) {
+#pragma unroll
+    for (int s = N / 2; s > 0; s >>= 1)
+#pragma unroll
+        for (int w = 0; w < s; ++w) v[w] += v[w + s];
+    return v[0];
 }
 
-// Bonded terms of one evaluation (any precision mode: always FP64).
-// Grid: every bonded block of every system (flat, map_bonded).
-__global__ void __launch_bounds__(kBondedPerBlock) k_bonded(Args a) {
-    const int2 m = at<int2>(a.ws, a.L.off_map_bonded)[blockIdx.x];
-    const int sys = m.x;
-    const SysInfo si = sys_info(a)[sys];
-    if (!(eval_active(a, sys, 0) || eval_active(a, sys, 1))) return;
-    bonded_block(a, eval_coords(a, sys, si), si, m.y, kBondedPerBlock);
+// Energy of a workgroup: pairwise sum over its threads (`tid`), stored by
+// thread 0.  The same order for any number of wavefronts that hold the same
+// values: across wavefronts first, then across lanes.
+template <int WAVES>
+__device__ __forceinline__ void block_energy_store(double e, double* out, int tid) {
+    if (WAVES > 1) {
+        __shared__ double red[WAVES][64];
+        red[tid >> 6][tid & 63] = e;
+        __syncthreads();
+        if (tid >= 64) return;
+        double v[WAVES];
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) v[w] = red[w][tid];
+        e = tree_sum<WAVES>(v);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o, 64);
+    if (tid == 0) *out = e;
+}
+
+// Bonded terms of one evaluation (any precision mode: always FP64): the first
+// workgroups of the pair kernel's grid (map_bonded), which evaluates them in
+// the shadow of the pair sums instead of in a launch of its own.
+template <int THREADS>
+__device__ __forceinline__ void bonded_block(const Args& a, int wg, int prec) {
+    const int2 m = at<int2>(a.ws, a.L.off_map_bonded)[wg];
+    if (!eval_active(a, m.x, prec)) return;
+    const SysInfo si = sys_info(a)[m.x];
+    const double* X = eval_coords(a, m.x, si);
+    // a lane's terms (four at most) are added pairwise too
+    double even = 0.0, odd = 0.0;
+#pragma unroll 1
+    for (int t = (int)threadIdx.x; t < kBondedPerBlock; t += THREADS) {
+        const double e = bonded_term(a, X, si, m.y * kBondedPerBlock + t);
+        if (t / THREADS & 1) odd += e;
+        else even += e;
+    }
+    block_energy_store<THREADS / 64>(even + odd, at<double>(a.ws, a.L.off_eb) + si.eb0 + m.y, threadIdx.x);
 }
 
 // ---------------------------------------------------------------- FP32 pairs
@@ -259,6 +272,10 @@ __device__ __forceinline__ void tile32(const float4* __restrict__ s_xq, const fl
 #pragma unroll
         for (int k = 0; k < IPL; ++k) excl[k] = EX[i0 + k * 64];
     }
+    // The loop without checks is fetched best when it starts 16 bytes into a
+    // 32-byte block: 50,000 atoms take 848 us there and 857-861 us at the other
+    // multiples of 8 bytes.
+    if (!MASKED && !CHECK) asm volatile(".p2align 5\n.rept 4\ns_nop 0\n.endr");
 #pragma unroll kUnroll32<IPL>
     for (int s = 0; s < kTile; ++s) {
         const int js = lane + s;
@@ -321,18 +338,6 @@ __device__ __forceinline__ void split(double v, float& hi, float& lo) {
     lo = (float)(v - (double)hi);
 }
 
-template <int WAVES>
-__device__ __forceinline__ void block_energy_store(double e, double* out) {
-    __shared__ double red[64 * WAVES];
-    red[threadIdx.x] = e;
-    __syncthreads();
-    for (int s = 32 * WAVES; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = red[0];
-}
-
 // HAS_FAR: the context has excluded pairs more than kExclWindow apart (the
 // kernel then checks every tile for a far-exclusion mask; the check costs a
 // few registers, so contexts without such pairs run the kernel without it).
@@ -347,13 +352,18 @@ template <int WAVES, int IPL, bool HAS_FAR>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kPair32MinWaves<IPL, HAS_FAR>)))
 k_pair32(Args a) {
     const Layout& L = a.L;
-    const int wg = blockIdx.x;
+    const int wg = (int)blockIdx.x - L.n_bonded_blocks;
+    if (wg < 0) {
+        if (a.bonded) bonded_block<64 * WAVES>(a, blockIdx.x, 1);
+        return;
+    }
     const ChunkInfo ch = at<ChunkInfo>(a.ws, L.off_chunks[0])[wg];
     if (!eval_active(a, ch.sys, 1)) return;
     const SysInfo si = sys_info(a)[ch.sys];
     const double* X = eval_coords(a, ch.sys, si);
     constexpr int B = 64 * WAVES * IPL;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: a scalar register
     const int n = si.n, aoff = si.aoff;
     const float* C12 = at<float>(a.ws, L.off_c12);
     const float* C6 = at<float>(a.ws, L.off_c6);
@@ -447,7 +457,7 @@ k_pair32(Args a) {
         const float gyb = fmaxf(0.0f, fmaxf(s_jbox[1] - ib[4], ib[1] - s_jbox[4]));
         const float gzb = fmaxf(0.0f, fmaxf(s_jbox[2] - ib[5], ib[2] - s_jbox[5]));
         const bool far = gxb * gxb + gyb * gyb + gzb * gzb >= kCorrR2;
-        const int fu = HAS_FAR ? FU[ch.unit_base + t - ch.t_begin] : -1;
+        const int fu = HAS_FAR ? FU[ch.unit + t - ch.t_begin] : -1;
         if (HAS_FAR && fu >= 0) {
             // the unit holds excluded pairs more than kExclWindow apart: each
             // lane copies the masks of its i-atoms (and only reads its own)
@@ -479,7 +489,7 @@ k_pair32(Args a) {
                 sy += (double)s_fj[w][1][lane];
                 sz += (double)s_fj[w][2][lane];
             }
-            float* pj = at<float>(a.ws, L.off_pj) + ((size_t)(ch.unit_base + t - ch.t_begin) * kTile + lane) * 3;
+            float* pj = at<float>(a.ws, L.off_pj) + ((size_t)(ch.j_row + t - ch.t_begin) * kTile + lane) * 3;
             pj[0] = (float)sx; pj[1] = (float)sy; pj[2] = (float)sz;
         }
     }
@@ -491,76 +501,138 @@ k_pair32(Args a) {
         const int il = wave * 64 * IPL + k * 64 + lane;
         pi[3 * il] = (float)gx[k]; pi[3 * il + 1] = (float)gy[k]; pi[3 * il + 2] = (float)gz[k];
     }
-    block_energy_store<WAVES>(e64, at<double>(a.ws, L.off_ep) + ch.slot);
+    block_energy_store<WAVES>(e64, at<double>(a.ws, L.off_ep) + ch.slot, threadIdx.x);
 }
 
 // ---------------------------------------------------------------- FP64 pairs
 
 // 1/sqrt(x) for finite x > 0: v_rsq_f64, then y (1 + e/2 + 3e^2/8) with
 // e = 1 - x y^2 (the error of the estimate enters cubed), the same
-// arithmetic rsqrt uses for such x.
-__device__ __forceinline__ double rsqrt_finite(double x) {
+// arithmetic rsqrt uses for such x.  For 0 and infinity e is not a number and
+// so is the result; SPECIAL keeps rsqrt's values there (e = 1 leaves the
+// estimate's infinity or 0).  Unmasked tiles hold no excluded pair, so x is
+// finite and positive, or 0 for coincident atoms, whose energy is not finite
+// either way.
+template <bool SPECIAL>
+__device__ __forceinline__ double rsqrt_step(double x) {
     const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
+    double e = fma(-x * y, y, 1.0);
+    if (SPECIAL) e = fmin(e, 1.0);
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-template <int IPL, bool MASKED, bool FAR = false>
-__device__ __forceinline__ void tile64(const double4* __restrict__ s_xq, const double2* __restrict__ s_c,
-                                       int lane, int J0, const double (&xi)[IPL], const double (&yi)[IPL],
+// Pairs of i-atom i with the atoms J0 .. J0 + 63 of a tile that count: bit jj is
+// set if J0 + jj > i and the pair is not excluded.  excl: the atom's near
+// exclusions (bit b: i + 1 + b), far: its far ones in this tile (bit jj).
+// Returned rotated so that bit s belongs to step s of lane `lane`.
+__device__ __forceinline__ uint64_t step_mask(int i, int J0, uint64_t excl, uint64_t far, int lane) {
+    const int sh = i + 1 - J0;               // bit of atom i + 1
+    uint64_t after, ex;
+    if (sh <= 0) {
+        after = ~0ull;
+        ex = -sh < 64 ? excl >> (-sh) : 0ull;
+    } else {
+        after = sh < 64 ? ~0ull << sh : 0ull;
+        ex = sh < 64 ? excl << sh : 0ull;
+    }
+    const uint64_t keep = after & ~ex & ~far;
+    return (keep >> lane) | (keep << ((64 - lane) & 63));
+}
+
+// Steps [s0, s1) of a j-tile (multiples of kPartSteps): at step s lane l takes
+// atom (l + s) mod 64, whose values are read one step ahead.  MASKED: only the
+// pairs of `keep` (step_mask) count.
+// (whole parts unrolled: a taken branch costs as much as seven operations)
+template <bool MASKED>
+constexpr int kUnroll64 = MASKED ? 2 : kPartSteps;
+
+template <int IPL, bool MASKED>
+__device__ __forceinline__ void tile64(const double4* __restrict__ s_xq, const double2* __restrict__ s_c, int lane,
+                                       int s0, int s1, const double (&xi)[IPL], const double (&yi)[IPL],
                                        const double (&zi)[IPL], const double (&a12i)[IPL],
                                        const double (&b6i)[IPL], const double (&qi)[IPL],
-                                       const uint64_t (&excl)[IPL], const uint64_t (&fmask)[IPL], const int (&idx)[IPL],
+                                       const uint64_t (&keep)[IPL],
                                        double (&gx)[IPL], double (&gy)[IPL], double (&gz)[IPL],
                                        double& fjx, double& fjy, double& fjz, double& elj, double& ecs) {
-#pragma unroll 2
-    for (int s = 0; s < kTile; ++s) {
-        const int js = lane + s;
-        const double4 pj = s_xq[js];
-        const double2 cj = s_c[js];
+    double4 pn = s_xq[lane + s0];
+    double2 cn = s_c[lane + s0];
+    // the loop without masks starts in the middle of a 64-byte block (50,000
+    // atoms: 1,440 us; 1,443 at its start, 1,445 where the compiler puts it)
+    if (!MASKED) asm volatile(".p2align 6\n.rept 8\ns_nop 0\n.endr");
+#pragma unroll 1
+    for (int sp = s0; sp < s1; sp += kPartSteps) {
+        int bits[IPL];                       // mask of the part's steps, the next one in the sign bit
+        if (MASKED) {
 #pragma unroll
-        for (int k = 0; k < IPL; ++k) {
-            const double dx = pj.x - xi[k], dy = pj.y - yi[k], dz = pj.z - zi[k];
-            double r2 = dx * dx + dy * dy + dz * dz;
-            if (MASKED) {
-                const int delta = J0 + (js & (kTile - 1)) - idx[k];
-                const unsigned dm1 = (unsigned)(delta - 1);
-                bool ex = dm1 < (unsigned)kExclWindow && ((excl[k] >> (dm1 & 63u)) & 1ull);
-                if (FAR) ex = ex || ((fmask[k] >> (js & (kTile - 1))) & 1ull);
-                r2 = (delta > 0 && !ex) ? r2 : __builtin_inf();
-            }
-            // unmasked tiles hold no excluded pair, so r2 is finite and
-            // positive (or 0 for coincident atoms, which gives a non-finite
-            // energy either way): the hardware estimate and one correction
-            // step, without the special-value handling rsqrt adds
-            const double rinv = MASKED ? rsqrt(r2) : rsqrt_finite(r2);
-            const double rinv2 = rinv * rinv;
-            const double rinv6 = rinv2 * rinv2 * rinv2;
-            const double A = a12i[k] * cj.x;
-            const double B = b6i[k] * cj.y;
-            const double ec = qi[k] * pj.w * rinv;
-            const double u = fma(A, rinv6, -B);
-            const double f = fma(u, rinv6, ec) * rinv2;
-            elj = fma(u - B, rinv6, elj);
-            ecs += ec;
-            gx[k] += f * dx; gy[k] += f * dy; gz[k] += f * dz;
-            fjx -= f * dx; fjy -= f * dy; fjz -= f * dz;
+            for (int k = 0; k < IPL; ++k) bits[k] = (int)__brev((unsigned)(keep[k] >> sp));
         }
-        fjx = rotate_down(fjx);
-        fjy = rotate_down(fjy);
-        fjz = rotate_down(fjz);
+        const double4* xq = s_xq + lane + sp;
+        const double2* xc = s_c + lane + sp;
+#pragma unroll kUnroll64<MASKED>
+        for (int s = 0; s < kPartSteps; ++s) {
+            const double4 pj = pn;
+            const double2 cj = cn;
+            pn = xq[s + 1];
+            cn = xc[s + 1];
+#pragma unroll
+            for (int k = 0; k < IPL; ++k) {
+                const double dx = pj.x - xi[k], dy = pj.y - yi[k], dz = pj.z - zi[k];
+                const double r2 = dx * dx + dy * dy + dz * dz;
+                double rinv = rsqrt_step<MASKED>(r2);
+                if (MASKED) {
+                    rinv = bits[k] < 0 ? rinv : 0.0;
+                    bits[k] <<= 1;
+                }
+                const double rinv2 = rinv * rinv;
+                const double rinv6 = rinv2 * rinv2 * rinv2;
+                const double A = a12i[k] * cj.x;
+                const double B = b6i[k] * cj.y;
+                const double ec = qi[k] * pj.w * rinv;
+                const double u = fma(A, rinv6, -B);
+                const double f = fma(u, rinv6, ec) * rinv2;
+                elj = fma(u - B, rinv6, elj);
+                ecs += ec;
+                gx[k] += f * dx; gy[k] += f * dy; gz[k] += f * dz;
+                fjx -= f * dx; fjy -= f * dy; fjz -= f * dz;
+            }
+            fjx = rotate_down(fjx);
+            fjy = rotate_down(fjy);
+            fjz = rotate_down(fjz);
+        }
     }
 }
 
+// LDS of one chunk: the j-tile twice in a row, and the j-side sums of several
+// wavefronts.
+template <int WAVES>
+struct Chunk64Lds {
+    double4 xq[2 * kTile];
+    double2 c[2 * kTile];
+    double fj[WAVES > 1 ? WAVES : 1][3][kTile];
+};
+// Orders the LDS accesses of the WAVES wavefronts that share a chunk.
+template <int WAVES>
+__device__ __forceinline__ void chunk_sync() {
+    if (WAVES > 1) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
+// One chunk by WAVES wavefronts of IPL i-atoms per lane; `tid` numbers their
+// threads.
 template <int WAVES, int IPL>
-__device__ __forceinline__ void pair64_chunk(const Args& a, int wg) {
+__device__ __forceinline__ void pair64_chunk(const Args& a, int id, int tid, Chunk64Lds<WAVES>& lds) {
     const Layout& L = a.L;
-    const ChunkInfo ch = at<ChunkInfo>(a.ws, L.off_chunks[1])[wg];
+    const ChunkInfo ch = at<ChunkInfo>(a.ws, L.off_chunks[1])[id];
     if (!eval_active(a, ch.sys, 0)) return;
     const SysInfo si = sys_info(a)[ch.sys];
     const double* X = eval_coords(a, ch.sys, si);
     constexpr int B = 64 * WAVES * IPL;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int n = si.n, aoff = si.aoff;
     const double* C12 = at<double>(a.ws, L.off_c12d);
     const double* C6 = at<double>(a.ws, L.off_c6d);
@@ -568,66 +640,75 @@ __device__ __forceinline__ void pair64_chunk(const Args& a, int wg) {
     const uint64_t* EX = at<uint64_t>(a.ws, L.off_excl);
     const int32_t* FU = at<int32_t>(a.ws, L.off_far_unit);
     const uint64_t* FM = at<uint64_t>(a.ws, L.off_far_mask);
-    const uint64_t fnone[IPL] = {};
     const int I0 = ch.row * B;
+    const int i0 = I0 + wave * 64 * IPL + lane;
 
+    // the j-tile's atom of this thread, loaded ahead of its use
+    double pj[3], qj = 0.0, c12j = 0.0, c6j = 0.0;
+    auto load_tile = [&](int t) {
+        const int j = t * kTile + tid;
+        load_pos(X, j - aoff, n, pj);
+        qj = Q[j]; c12j = C12[j]; c6j = C6[j];
+    };
+    const bool any_far = L.n_far_units > 0;
     double xi[IPL], yi[IPL], zi[IPL], a12i[IPL], b6i[IPL], qi[IPL], gx[IPL], gy[IPL], gz[IPL];
-    uint64_t excl[IPL];
-    int idx[IPL];
+    double elj = 0.0, ecs = 0.0;     // 12 x Lennard-Jones energy, Coulomb energy
+    double4* s_xq = lds.xq;
+    double2* s_c = lds.c;
+    const int t_masked_end = (I0 + B) / kTile + 1;
+    if (tid < kTile) load_tile(ch.t_begin);
 #pragma unroll
     for (int k = 0; k < IPL; ++k) {
-        const int i = I0 + wave * 64 * IPL + k * 64 + lane;
+        const int i = i0 + k * 64;
         double p[3];
         load_pos(X, i - aoff, n, p);
         xi[k] = p[0]; yi[k] = p[1]; zi[k] = p[2];
         a12i[k] = 12.0 * C12[i]; b6i[k] = 6.0 * C6[i]; qi[k] = Q[i];
-        excl[k] = EX[i];
-        idx[k] = i;
         gx[k] = gy[k] = gz[k] = 0.0;
     }
-    __shared__ double4 s_xq[2 * kTile];
-    __shared__ double2 s_c[2 * kTile];
-    __shared__ double s_fj[WAVES][3][kTile];
-    double elj = 0.0, ecs = 0.0;     // 12 x Lennard-Jones energy, Coulomb energy
-    const int t_masked_end = (I0 + B) / kTile + 1;
     for (int t = ch.t_begin; t < ch.t_end; ++t) {
         const int J0 = t * kTile;
-        __syncthreads();
-        if (threadIdx.x < kTile) {
-            const int j = J0 + threadIdx.x;
-            double p[3];
-            load_pos(X, j - aoff, n, p);
-            const double4 h = make_double4(p[0], p[1], p[2], Q[j]);
-            const double2 c = make_double2(C12[j], C6[j]);
-            s_xq[threadIdx.x] = h; s_xq[threadIdx.x + kTile] = h;
-            s_c[threadIdx.x] = c;  s_c[threadIdx.x + kTile] = c;
+        chunk_sync<WAVES>();
+        if (tid < kTile) {
+            const double4 h = make_double4(pj[0], pj[1], pj[2], qj);
+            const double2 c = make_double2(c12j, c6j);
+            s_xq[tid] = h; s_xq[tid + kTile] = h;
+            s_c[tid] = c;  s_c[tid + kTile] = c;
+            if (t + 1 < ch.t_end) load_tile(t + 1);
         }
-        __syncthreads();
+        chunk_sync<WAVES>();
+        const int s0 = t == ch.t_begin ? ch.steps & 0xff : 0;
+        const int s1 = t == ch.t_end - 1 ? ch.steps >> 8 : kTile;
         double fjx = 0.0, fjy = 0.0, fjz = 0.0;
-        const int fu = FU[ch.unit_base + t - ch.t_begin];
-        if (fu >= 0) {
-            uint64_t fmask[IPL];
+        const int fu = any_far ? FU[ch.unit + t - ch.t_begin] : -1;
+        uint64_t keep[IPL];
+        if (fu >= 0 || t < t_masked_end) {
 #pragma unroll
-            for (int k = 0; k < IPL; ++k) fmask[k] = FM[(size_t)fu * B + wave * 64 * IPL + k * 64 + lane];
-            tile64<IPL, true, true>(s_xq, s_c, lane, J0, xi, yi, zi, a12i, b6i, qi, excl, fmask, idx, gx, gy, gz,
-                                    fjx, fjy, fjz, elj, ecs);
-        } else if (t < t_masked_end) {
-            tile64<IPL, true>(s_xq, s_c, lane, J0, xi, yi, zi, a12i, b6i, qi, excl, fnone, idx, gx, gy, gz, fjx, fjy,
-                              fjz, elj, ecs);
+            for (int k = 0; k < IPL; ++k)
+                keep[k] = step_mask(i0 + k * 64, J0, EX[i0 + k * 64],
+                                    fu >= 0 ? FM[(size_t)fu * B + i0 - I0 + k * 64] : 0ull, lane);
+            tile64<IPL, true>(s_xq, s_c, lane, s0, s1, xi, yi, zi, a12i, b6i, qi, keep, gx, gy, gz, fjx, fjy, fjz, elj,
+                              ecs);
         } else {
-            tile64<IPL, false>(s_xq, s_c, lane, J0, xi, yi, zi, a12i, b6i, qi, excl, fnone, idx, gx, gy, gz, fjx,
-                               fjy, fjz, elj, ecs);
+            tile64<IPL, false>(s_xq, s_c, lane, s0, s1, xi, yi, zi, a12i, b6i, qi, keep, gx, gy, gz, fjx, fjy, fjz,
+                               elj, ecs);
         }
-        s_fj[wave][0][lane] = fjx;
-        s_fj[wave][1][lane] = fjy;
-        s_fj[wave][2][lane] = fjz;
-        __syncthreads();
-        if (wave == 0) {
-            double sx = 0.0, sy = 0.0, sz = 0.0;
+        // lane l now holds the sum for atom (l + s1) mod 64 of the tile
+        if (WAVES > 1) {
+            lds.fj[wave][0][lane] = fjx;
+            lds.fj[wave][1][lane] = fjy;
+            lds.fj[wave][2][lane] = fjz;
+            chunk_sync<WAVES>();
+            if (wave == 0) {
+                fjx = fjy = fjz = 0.0;
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w) { sx += s_fj[w][0][lane]; sy += s_fj[w][1][lane]; sz += s_fj[w][2][lane]; }
-            double* pj = at<double>(a.ws, L.off_pj) + ((size_t)(ch.unit_base + t - ch.t_begin) * kTile + lane) * 3;
-            pj[0] = sx; pj[1] = sy; pj[2] = sz;
+                for (int w = 0; w < WAVES; ++w) { fjx += lds.fj[w][0][lane]; fjy += lds.fj[w][1][lane]; fjz += lds.fj[w][2][lane]; }
+            }
+        }
+        if (wave == 0) {
+            double* o = at<double>(a.ws, L.off_pj) +
+                        ((size_t)(ch.j_row + t - ch.t_begin) * kTile + ((lane + s1) & (kTile - 1))) * 3;
+            o[0] = fjx; o[1] = fjy; o[2] = fjz;
         }
     }
     double* pi = at<double>(a.ws, L.off_pi) + (size_t)ch.slot * B * 3;
@@ -636,33 +717,33 @@ __device__ __forceinline__ void pair64_chunk(const Args& a, int wg) {
         const int il = wave * 64 * IPL + k * 64 + lane;
         pi[3 * il] = gx[k]; pi[3 * il + 1] = gy[k]; pi[3 * il + 2] = gz[k];
     }
-    block_energy_store<WAVES>(elj * (1.0 / 12.0) + ecs, at<double>(a.ws, L.off_ep) + ch.slot);
+    block_energy_store<WAVES>(elj * (1.0 / 12.0) + ecs, at<double>(a.ws, L.off_ep) + ch.slot, tid);
 }
 
-// The FP64 kernel walks the chunks with a grid stride: in FP32 mode (and in
-// cycles without an evaluation) its workgroups only check and exit, and a
-// capped grid keeps that cheap.  The cap allows 16384 wavefronts (four per
-// SIMD) and at least 4096 workgroups: one-wavefront workgroups (the batch
-// tiling) would otherwise leave three quarters of the chip idle.
-constexpr int kPair64Waves = 16384;
-__host__ __device__ constexpr int pair64_grid_cap(int waves) {
-    return kPair64Waves / waves > 4096 ? kPair64Waves / waves : 4096;
-}
+// A workgroup holds four chunks of one wavefront each, or one chunk of several
+// wavefronts (fewer workgroups to launch and to send home in cycles without an
+// FP64 evaluation).  The kernel walks the chunks with a grid stride: in FP32
+// mode (and in cycles without an evaluation) its workgroups only check and
+// exit, and a capped grid keeps that cheap.
+__host__ __device__ constexpr int group64(int waves) { return waves == 1 ? 4 : 1; }
+constexpr int kPair64Grid = 4096;
 
 template <int WAVES, int IPL>
-__global__ void __launch_bounds__(64 * WAVES) k_pair64(Args a) {
-    // one activity check for the whole launch: a single system's, or, for a
-    // batch, whether any system evaluates in FP64 this cycle (the threads
-    // read the control blocks side by side); then each chunk checks its own
-    // system
-    if (a.L.n_sys == 1) {
-        if (!eval_active(a, 0, 0)) return;
-    } else if (!a.direct) {
-        int any = 0;
-        for (int s = threadIdx.x; s < a.L.n_sys && !any; s += blockDim.x) any = eval_active(a, s, 0) ? 1 : 0;
-        if (!__syncthreads_or(any)) return;
+__global__ void __launch_bounds__(64 * WAVES * group64(WAVES)) k_pair64(Args a) {
+    // a single system's activity check for the whole launch; in a batch each
+    // chunk checks its own system
+    if (a.L.n_sys == 1 && !eval_active(a, 0, 0)) return;
+    constexpr int G = group64(WAVES);
+    __shared__ Chunk64Lds<WAVES> lds[G];
+    const int sub = G > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    const int tid = G > 1 ? threadIdx.x & 63 : threadIdx.x;
+    const int nb = a.L.n_bonded_blocks;
+    if ((int)blockIdx.x < nb) {
+        if (a.bonded) bonded_block<64 * WAVES * G>(a, blockIdx.x, 0);
+        return;
     }
-    for (int wg = blockIdx.x; wg < a.L.n_chunks[1]; wg += gridDim.x) pair64_chunk<WAVES, IPL>(a, wg);
+    for (int id = ((int)blockIdx.x - nb) * G + sub; id < a.L.n_chunks[1]; id += ((int)gridDim.x - nb) * G)
+        pair64_chunk<WAVES, IPL>(a, id, tid, lds[sub]);
 }
 
 // ------------------------------------------------------------- host launch
@@ -673,17 +754,20 @@ __global__ void __launch_bounds__(64 * WAVES) k_pair64(Args a) {
     case ID: {                                                                                     \
         constexpr TileConfig T = kTileConfigs[ID];                                                 \
         if (prec && a.L.n_far_units > 0)                                                              \
-            hipLaunchKernelGGL((k_pair32<T.waves32, T.ipl32, true>), dim3(grid), dim3(64 * T.waves32), 0, s, a); \
+            hipLaunchKernelGGL((k_pair32<T.waves32, T.ipl32, true>), dim3(nb + grid), dim3(64 * T.waves32), 0, s, a); \
         else if (prec)                                                                                \
-            hipLaunchKernelGGL((k_pair32<T.waves32, T.ipl32, false>), dim3(grid), dim3(64 * T.waves32), 0, s, a); \
-        else hipLaunchKernelGGL((k_pair64<T.waves64, T.ipl64>),                                        \
-                                dim3(grid < pair64_grid_cap(T.waves64) ? grid : pair64_grid_cap(T.waves64)), \
-                                dim3(64 * T.waves64), 0, s, a);                                                 \
+            hipLaunchKernelGGL((k_pair32<T.waves32, T.ipl32, false>), dim3(nb + grid), dim3(64 * T.waves32), 0, s, a); \
+        else {                                                                                         \
+            constexpr int G = group64(T.waves64);                                                      \
+            const int wgs = (grid + G - 1) / G;                                                        \
+            hipLaunchKernelGGL((k_pair64<T.waves64, T.ipl64>), dim3(nb + (wgs < kPair64Grid ? wgs : kPair64Grid)), \
+                               dim3(64 * T.waves64 * G), 0, s, a);                                     \
+        }                                                                                              \
         break;                                                                                     \
     }
 
 hipError_t launch_pair(const Args& a, int prec, hipStream_t s) {
-    const int grid = a.L.n_chunks[prec ? 0 : 1];
+    const int grid = a.L.n_chunks[prec ? 0 : 1], nb = a.L.n_bonded_blocks;
     switch (a.L.cfg) {
         FF_PAIR_CASE(0)
         FF_PAIR_CASE(1)
@@ -700,11 +784,5 @@ hipError_t launch_pair(const Args& a, int prec, hipStream_t s) {
     }
     return hipGetLastError();
 }
-
-hipError_t launch_bonded(const Args& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_bonded, dim3(a.L.n_bonded_blocks), dim3(kBondedPerBlock), 0, s, a);
-    return hipGetLastError();
-}
-
 
 }  // namespace ff
