@@ -149,7 +149,9 @@ struct Ctl {
     int32_t trace_cap, n_trace;
     BatchState* batch;       // batch-wide counters
     int32_t n_atoms;         // atoms of this system
-
+    // workgroups of the running finalize and accept pass that are done (the
+    // last one of each goes on with the reduction and sets it back to 0)
+    uint32_t fin_ticket, acc_ticket;
 };
 
 // ------------------------------------------------------- pair tile configs
