@@ -75,6 +75,14 @@ struct BatchState {
     uint32_t pad_;
 };
 
+// Batches of iteration graphs on a stream: one runs while the next is queued.
+constexpr int kBatchesQueued = 2;
+// What a minimization returns for a system (written to pinned host memory).
+struct ResultDev {
+    int32_t term, iters, evals, evals64;
+    double energy, ginf, g2;
+};
+
 struct MinParamsDev {
     int32_t method, m, max_iter, precision, linesearch, ls_K, cg_restart, certify, cg_beta, ls_g0, fgm_restart;
     double tol, h_init, k_plus, k_minus, eps_h, hb_alpha, hb_beta;

@@ -628,6 +628,32 @@ __global__ void k_reset_batch(Args a) {
     reset_batch(at<BatchState>(a.ws, a.L.off_batch));
 }
 
+// Caller's coordinates into slot 0 (before a minimization starts) and the
+// result slot's back.  Grid: flat over every system's 3n elements (map_vec).
+__global__ void __launch_bounds__(kFinBlock) k_load_points(Args a, const double* xyz) {
+    const int2 mb = at<int2>(a.ws, a.L.off_map_vec)[blockIdx.x];
+    const SysInfo si = sys_info(a)[mb.x];
+    const int i = mb.y * kFinBlock + threadIdx.x;
+    if (i < 3 * si.n) vec(a, V_X0, si)[i] = xyz[3 * (size_t)si.uoff + i];
+}
+
+__global__ void __launch_bounds__(kFinBlock) k_store_results(Args a, double* xyz, ResultDev* res) {
+    const int2 mb = at<int2>(a.ws, a.L.off_map_vec)[blockIdx.x];
+    const SysInfo si = sys_info(a)[mb.x];
+    const Ctl* c = ctl_at(a, mb.x);
+    const int slot = c->result_slot;
+    const int i = mb.y * kFinBlock + threadIdx.x;
+    if (i < 3 * si.n) xyz[3 * (size_t)si.uoff + i] = vec(a, V_X0 + slot, si)[i];
+    if (i == 0)
+        res[mb.x] = ResultDev{c->term, c->iters - c->iters_base, c->evals, c->evals64, c->e[slot], c->ginf[slot],
+                              c->g2[slot]};
+}
+
+// The batch counters to pinned host memory.
+__global__ void k_report(Args a, BatchState* to) {
+    if (threadIdx.x == 0) *to = *at<BatchState>(a.ws, a.L.off_batch);
+}
+
 // Marks every system idle and zeroes the batch counters (after ff_create).
 __global__ void k_reset_ctl(Args a) {
     if (threadIdx.x != 0) return;
@@ -674,6 +700,21 @@ hipError_t launch_cycle_vec(const Args& a, int which, hipStream_t s) {
         hipLaunchKernelGGL(k_prepare, dim3(a.L.n_vec_blocks), dim3(kFinBlock), 0, s, a);
     else
         hipLaunchKernelGGL(k_accept, dim3(a.L.n_acc_blocks, a.L.acc_rows), dim3(kFinBlock), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_load_points(const Args& a, const double* xyz, hipStream_t s) {
+    hipLaunchKernelGGL(k_load_points, dim3(a.L.n_vec_blocks), dim3(kFinBlock), 0, s, a, xyz);
+    return hipGetLastError();
+}
+
+hipError_t launch_store_results(const Args& a, double* xyz, ResultDev* res, hipStream_t s) {
+    hipLaunchKernelGGL(k_store_results, dim3(a.L.n_vec_blocks), dim3(kFinBlock), 0, s, a, xyz, res);
+    return hipGetLastError();
+}
+
+hipError_t launch_report(const Args& a, BatchState* to, hipStream_t s) {
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, a, to);
     return hipGetLastError();
 }
 
