@@ -1140,7 +1140,7 @@ int32_t ff_get_trace(ff_ctx* c, double* host_out, int32_t max_entries, void* str
     stream = stream ? stream : (void*)c->own;
     hipStream_t st = (hipStream_t)stream;
     int32_t n = 0;
-    if (hipMemcpyAsync(&n, c->ws + c->L.off_ctl + offsetof(Ctl, n_trace), 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+    if (hipMemcpyAsync(&n, c->ws + c->L.off_ctl + offsetof(CtlState, n_trace), 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return fail(FF_ERR_HIP, "trace count copy failed");
     n = std::min(n, max_entries);

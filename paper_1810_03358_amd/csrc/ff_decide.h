@@ -58,7 +58,7 @@ __device__ inline bool rank_less(double f1, double h1, double f2, double h2) {
     return k1 < k2 || (k1 == k2 && h1 < h2);
 }
 
-__device__ inline int alloc_slot(const Ctl* c) {
+__device__ inline int alloc_slot(const CtlState* c) {
     for (int s = 0; s < kNumSlots; ++s) {
         if (s == c->cur || s == c->prev_x || s == c->best || s == c->w || s == c->ls_base || s == c->ls_best)
             continue;
@@ -68,7 +68,7 @@ __device__ inline int alloc_slot(const Ctl* c) {
 }
 
 // ------------------------------------------------------------ requests
-__device__ inline void request_eval(Ctl* c, int mode, int target, int want_slope) {
+__device__ inline void request_eval(CtlState* c, int mode, int target, int want_slope) {
     c->action = ACT_EVAL;
     c->point_mode = mode;
     c->target = target;
@@ -81,13 +81,13 @@ __device__ inline void request_eval(Ctl* c, int mode, int target, int want_slope
 // The system needs no FP32 evaluation any more (it switched to FP64 or it
 // stops): counted once per ff_minimize call, so that the host can leave the
 // FP32 pair kernel out of the iteration graph once every system is there.
-__device__ inline void release_fp32(Ctl* c) {
+__device__ inline void release_fp32(CtlState* c) {
     if (c->fp32_released) return;
     c->fp32_released = 1;
     if (c->batch) atomicAdd(&c->batch->n_fp64, 1u);
 }
 
-__device__ inline void finish_done(Ctl* c, int slot) {
+__device__ inline void finish_done(CtlState* c, int slot) {
     release_fp32(c);
     c->result_slot = slot;
     c->phase = PH_DONE;
@@ -97,7 +97,7 @@ __device__ inline void finish_done(Ctl* c, int slot) {
     if (c->batch) atomicAdd(&c->batch->n_done, 1u);
 }
 
-__device__ inline void finish(Ctl* c, int term) {
+__device__ inline void finish(CtlState* c, int term) {
     release_fp32(c);
     c->term = term;
     const int slot = (c->p.method == M_FGM && c->best >= 0) ? c->best : c->cur;
@@ -111,11 +111,11 @@ __device__ inline void finish(Ctl* c, int term) {
     finish_done(c, slot);
 }
 
-__device__ inline void lbfgs_clear(Ctl* c);
+__device__ inline void lbfgs_clear(CtlState* c);
 
 // OGM restart at the current point: anchor x^0 := x^k, t := 1, and the
 // weighted gradient sum := the current gradient.
-__device__ inline void ogm_restart(Ctl* c) {
+__device__ inline void ogm_restart(CtlState* c) {
     c->prev_x = c->cur;
     c->ogm_t = 1.0;
     c->ogm_s_anchor = 1;
@@ -126,7 +126,7 @@ __device__ inline void ogm_restart(Ctl* c) {
 // stored L-BFGS pairs and the CG direction were built from FP32 gradients
 // and their products with g would no longer match the FP64 gradient, so the
 // next direction starts again from -g.
-__device__ inline void escalate(Ctl* c, int slot) {
+__device__ inline void escalate(CtlState* c, int slot) {
     release_fp32(c);
     c->escalated = 1;
     c->prec_now = P_FP64;
@@ -141,7 +141,7 @@ __device__ inline void escalate(Ctl* c, int slot) {
 }
 
 // ----------------------------------------------------------- line search
-__device__ inline void ls_trial(Ctl* c, double h, bool first) {
+__device__ inline void ls_trial(CtlState* c, double h, bool first) {
     c->ls_hcur = h;
     c->h = h;
     c->base = c->ls_base;
@@ -149,7 +149,7 @@ __device__ inline void ls_trial(Ctl* c, double h, bool first) {
     request_eval(c, first ? PM_DIR_TRIAL : PM_TRIAL, t, first ? 1 : 0);
 }
 
-__device__ inline void ls_start(Ctl* c, int base, double h0, int kind, bool first) {
+__device__ inline void ls_start(CtlState* c, int base, double h0, int kind, bool first) {
     c->phase = PH_LS;
     c->ls_kind = kind;
     c->ls_base = base;
@@ -163,8 +163,8 @@ __device__ inline void ls_start(Ctl* c, int base, double h0, int kind, bool firs
     ls_trial(c, (kind == LSK_PAR && !c->p.ls_g0) ? -0.5 * h0 : h0, first);
 }
 
-__device__ void ls_success(Ctl* c, int slot, double h);
-__device__ void ls_failed(Ctl* c);
+__device__ void ls_success(CtlState* c, int slot, double h);
+__device__ void ls_failed(CtlState* c);
 
 __device__ inline double parabola3_vertex(double ha, double fa, double hb, double fb, double hc, double fc,
                                           bool& ok) {
@@ -179,7 +179,7 @@ __device__ inline double parabola3_vertex(double ha, double fa, double hb, doubl
     return h;
 }
 
-__device__ inline void ls_after_trial(Ctl* c) {
+__device__ inline void ls_after_trial(CtlState* c) {
     const int t = c->target;
     const double f = c->e[t];
     const double h = c->ls_hcur;
@@ -280,16 +280,16 @@ __device__ inline void ls_after_trial(Ctl* c) {
 }
 
 // ------------------------------------------------------------- directions
-__device__ inline int ring_slot(const Ctl* c, int i) {
+__device__ inline int ring_slot(const CtlState* c, int i) {
     const int q = c->hist_head + i;
     return q >= c->hist_m ? q - c->hist_m : q;
 }
 __device__ inline int gpos_s(int slot) { return slot; }
 __device__ inline int gpos_y(int slot) { return kMaxM + slot; }
 constexpr int kGposG = 2 * kMaxM;
-__device__ inline double& gram_at(Ctl* c, int a, int b) { return c->gram[a * kGramDim + b]; }
+__device__ inline double& gram_at(double* gram, int a, int b) { return gram[a * kGramDim + b]; }
 
-__device__ inline void lbfgs_clear(Ctl* c) {
+__device__ inline void lbfgs_clear(CtlState* c) {
     c->hist_n = 0;
     c->hist_head = 0;
     c->hist_m = c->p.m;
@@ -300,7 +300,7 @@ __device__ inline void lbfgs_clear(Ctl* c) {
     c->spare_y_next = V_Y0 + 1;
 }
 
-__device__ inline void set_steepest(Ctl* c) {
+__device__ inline void set_steepest(CtlState* c) {
     c->n_terms = 1;
     c->term_vec[0] = V_G0 + c->cur;
     c->term_coef[0] = -1.0;
@@ -311,7 +311,7 @@ __device__ inline void set_steepest(Ctl* c) {
 // Starts the next iteration at the current point.  For L-BFGS with stored
 // pairs the direction's terms were filled by the workgroup step that ran
 // just before (lb_ready); they are used here or dropped.
-__device__ inline void begin_iteration(Ctl* c) {
+__device__ inline void begin_iteration(CtlState* c) {
     const MinParamsDev& p = c->p;
     const int lb_ready = c->lb_ready;
     c->lb_ready = 0;
@@ -428,7 +428,7 @@ __device__ inline void begin_iteration(Ctl* c) {
     ls_start(c, p.method == M_FGM ? c->w : c->cur, c->h_prev, primary, true);
 }
 
-__device__ inline void fgm_after_momentum(Ctl* c) {
+__device__ inline void fgm_after_momentum(CtlState* c) {
     const int w = c->target;
     const bool ok = isfinite(c->e[w]) && isfinite(c->g2[w]) && c->g2[w] > 0.0;
     if (!ok) { ls_failed(c); return; }
@@ -442,7 +442,7 @@ __device__ inline void fgm_after_momentum(Ctl* c) {
     ls_start(c, w, c->h_prev, primary, true);
 }
 
-__device__ void ls_success(Ctl* c, int slot, double h) {
+__device__ void ls_success(CtlState* c, int slot, double h) {
     // FP32 mode: a decrease below 2^-23 |E| (twice the FP32 unit roundoff;
     // the measured FP32 error of E is about 1e-7 |E|) cannot be told from
     // rounding, so the next iteration switches to FP64
@@ -462,7 +462,7 @@ __device__ void ls_success(Ctl* c, int slot, double h) {
     c->action = ACT_NONE;
 }
 
-__device__ void ls_failed(Ctl* c) {
+__device__ void ls_failed(CtlState* c) {
     const MinParamsDev& p = c->p;
     if (p.precision == P_FP32 && !c->escalated) {
         c->ls_base = -1; c->ls_best = -1;
@@ -511,10 +511,65 @@ __device__ inline double cg_beta(int variant, double gg, double gngn, double gng
     return isfinite(b) ? b : 0.0;
 }
 
-// After the accept pass, first part: method state from the dot products.
-// Returns true when L-BFGS direction coefficients have to be computed (by the
-// whole workgroup) before accept_finish starts the next iteration.
-__device__ inline bool accept_update(Ctl* c, const double* dots) {
+// After the accept pass of L-BFGS, by a whole workgroup: the new pair enters
+// the memory (its products the Gram matrix) unless <s, y> is too small, and the
+// gradient's products are replaced.  Returns true (in every thread) when
+// direction coefficients have to be computed before accept_finish starts the
+// next iteration.
+// dots: [0] <s,y> [1] <y,y> [2] <s,s> [3] <g,s> [4] <g,y> [5] <g,g>, then for
+// the pair in slot q: dots[6 + 6q ..] = <s,S_q> <s,Y_q> <y,S_q> <y,Y_q>
+// <g,S_q> <g,Y_q>
+__device__ inline bool lbfgs_update(CtlState* c, double* gram, const double* dots) {
+    const double sy = dots[0], yy = dots[1];
+    const int n_old = c->hist_n;
+    const bool full = n_old == c->hist_m;
+    const bool take = sy > kEpsMach * yy;
+    // the new pair takes the slot of the oldest one when the memory is full
+    const int q = full ? c->hist_head : ring_slot(c, n_old);
+    const int i = threadIdx.x;
+    if (i < n_old && !(take && full && i == 0)) {
+        const int r = ring_slot(c, i);
+        const double* d6 = dots + 6 + 6 * r;
+        if (take) {
+            gram_at(gram, gpos_s(q), gpos_s(r)) = gram_at(gram, gpos_s(r), gpos_s(q)) = d6[0];
+            gram_at(gram, gpos_s(q), gpos_y(r)) = gram_at(gram, gpos_y(r), gpos_s(q)) = d6[1];
+            gram_at(gram, gpos_y(q), gpos_s(r)) = gram_at(gram, gpos_s(r), gpos_y(q)) = d6[2];
+            gram_at(gram, gpos_y(q), gpos_y(r)) = gram_at(gram, gpos_y(r), gpos_y(q)) = d6[3];
+        }
+        gram_at(gram, kGposG, gpos_s(r)) = gram_at(gram, gpos_s(r), kGposG) = d6[4];
+        gram_at(gram, kGposG, gpos_y(r)) = gram_at(gram, gpos_y(r), kGposG) = d6[5];
+    }
+    __syncthreads();                         // every thread has read the ring
+    if (threadIdx.x == 0) {
+        gram_at(gram, kGposG, kGposG) = dots[5];
+        if (take) {
+            gram_at(gram, gpos_s(q), gpos_s(q)) = dots[2];
+            gram_at(gram, gpos_s(q), gpos_y(q)) = gram_at(gram, gpos_y(q), gpos_s(q)) = sy;
+            gram_at(gram, gpos_y(q), gpos_y(q)) = yy;
+            gram_at(gram, kGposG, gpos_s(q)) = gram_at(gram, gpos_s(q), kGposG) = dots[3];
+            gram_at(gram, kGposG, gpos_y(q)) = gram_at(gram, gpos_y(q), kGposG) = dots[4];
+            const int drop_s = c->hist_s[q], drop_y = c->hist_y[q];
+            c->hist_s[q] = c->spare_s;
+            c->hist_y[q] = c->spare_y;
+            c->rho[q] = 1.0 / sy;
+            if (full) {
+                c->hist_head = c->hist_head + 1 == c->hist_m ? 0 : c->hist_head + 1;
+                c->spare_s = drop_s;
+                c->spare_y = drop_y;
+            } else {
+                c->hist_n = n_old + 1;
+                c->spare_s = c->spare_s_next++;
+                c->spare_y = c->spare_y_next++;
+            }
+        }
+        c->cur = c->acc_new;
+    }
+    __syncthreads();
+    return c->hist_n > 0;
+}
+
+// The same of the other methods, by one thread.
+__device__ inline void accept_update(CtlState* c, const double* dots) {
     const MinParamsDev& p = c->p;
     const int nw = c->acc_new, old = c->acc_old;
     switch (p.method) {
@@ -534,56 +589,6 @@ __device__ inline bool accept_update(Ctl* c, const double* dots) {
         }
         c->cur = nw;
         break;
-    }
-    case M_LBFGS: {
-        // dots: [0] <s,y> [1] <y,y> [2] <s,s> [3] <g,s> [4] <g,y> [5] <g,g>,
-        // then for the pair in slot q: dots[6 + 6q ..] = <s,S_q> <s,Y_q>
-        // <y,S_q> <y,Y_q> <g,S_q> <g,Y_q>
-        const double sy = dots[0], yy = dots[1];
-        const int n_old = c->hist_n;
-        const bool full = n_old == c->hist_m;
-        if (sy > kEpsMach * yy) {
-            // the new pair takes the slot of the oldest one when the memory is full
-            const int q = full ? c->hist_head : ring_slot(c, n_old);
-            const int drop_s = c->hist_s[q], drop_y = c->hist_y[q];
-            for (int i = full ? 1 : 0; i < n_old; ++i) {
-                const int r = ring_slot(c, i);
-                const double* d6 = dots + 6 + 6 * r;
-                gram_at(c, gpos_s(q), gpos_s(r)) = gram_at(c, gpos_s(r), gpos_s(q)) = d6[0];
-                gram_at(c, gpos_s(q), gpos_y(r)) = gram_at(c, gpos_y(r), gpos_s(q)) = d6[1];
-                gram_at(c, gpos_y(q), gpos_s(r)) = gram_at(c, gpos_s(r), gpos_y(q)) = d6[2];
-                gram_at(c, gpos_y(q), gpos_y(r)) = gram_at(c, gpos_y(r), gpos_y(q)) = d6[3];
-                gram_at(c, kGposG, gpos_s(r)) = gram_at(c, gpos_s(r), kGposG) = d6[4];
-                gram_at(c, kGposG, gpos_y(r)) = gram_at(c, gpos_y(r), kGposG) = d6[5];
-            }
-            gram_at(c, gpos_s(q), gpos_s(q)) = dots[2];
-            gram_at(c, gpos_s(q), gpos_y(q)) = gram_at(c, gpos_y(q), gpos_s(q)) = sy;
-            gram_at(c, gpos_y(q), gpos_y(q)) = yy;
-            gram_at(c, kGposG, gpos_s(q)) = gram_at(c, gpos_s(q), kGposG) = dots[3];
-            gram_at(c, kGposG, gpos_y(q)) = gram_at(c, gpos_y(q), kGposG) = dots[4];
-            c->hist_s[q] = c->spare_s;
-            c->hist_y[q] = c->spare_y;
-            c->rho[q] = 1.0 / sy;
-            if (full) {
-                c->hist_head = c->hist_head + 1 == c->hist_m ? 0 : c->hist_head + 1;
-                c->spare_s = drop_s;
-                c->spare_y = drop_y;
-            } else {
-                c->hist_n = n_old + 1;
-                c->spare_s = c->spare_s_next++;
-                c->spare_y = c->spare_y_next++;
-            }
-        } else {
-            for (int i = 0; i < n_old; ++i) {
-                const int r = ring_slot(c, i);
-                const double* d6 = dots + 6 + 6 * r;
-                gram_at(c, kGposG, gpos_s(r)) = gram_at(c, gpos_s(r), kGposG) = d6[4];
-                gram_at(c, kGposG, gpos_y(r)) = gram_at(c, gpos_y(r), kGposG) = d6[5];
-            }
-        }
-        gram_at(c, kGposG, kGposG) = dots[5];
-        c->cur = nw;
-        return c->hist_n > 0;
     }
     case M_HB:
         c->prev_x = c->cur;          // x^{k-1}
@@ -607,13 +612,14 @@ __device__ inline bool accept_update(Ctl* c, const double* dots) {
         if (c->e[nw] < c->e[c->best]) c->best = nw;
         break;
     }
+    default:
+        break;
     }
-    return false;
 }
 
 // After the accept pass, second part: trace entry, iteration count, next
 // iteration.
-__device__ inline void accept_finish(Ctl* c) {
+__device__ inline void accept_finish(CtlState* c) {
     const int nw = c->acc_new;
     const int ti = c->iters - c->iters_base;
     if (c->trace_ptr && ti < c->trace_cap) {
@@ -628,7 +634,7 @@ __device__ inline void accept_finish(Ctl* c) {
 }
 
 // After an evaluation (finalize's last workgroup).
-__device__ inline void after_eval(Ctl* c) {
+__device__ inline void after_eval(CtlState* c) {
     c->evals += 1;
     if (c->batch) atomicAdd(&c->batch->evals, 1u);
     if (c->prec == P_FP64) c->evals64 += 1;

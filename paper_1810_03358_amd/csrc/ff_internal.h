@@ -88,7 +88,9 @@ struct MinParamsDev {
     double tol, h_init, k_plus, k_minus, eps_h, hb_alpha, hb_beta;
 };
 
-struct Ctl {
+// Control block of a system without its Gram matrix: what the decision step
+// works on (the last workgroup of a pass holds it in LDS meanwhile).
+struct CtlState {
     // ---- request for the next evaluation cycle (written by the decision step)
     int32_t action;
     int32_t point_mode;
@@ -147,8 +149,6 @@ struct Ctl {
     int32_t spare_s, spare_y;                        // vector ids for the next pair
     int32_t spare_s_next, spare_y_next;              // first never-used ids
     double rho[kMaxM];                               // 1 / <s, y> by slot
-    // Gram matrix of {s of slot q at q, y of slot q at kMaxM + q, g at 2 kMaxM}
-    double gram[kGramDim * kGramDim];
     int32_t lb_ready;        // direction coefficients for the next iteration:
                              // 1 computed (terms filled), -1 not a descent direction, 0 none
     int32_t result_slot;
@@ -157,6 +157,11 @@ struct Ctl {
     int32_t trace_cap, n_trace;
     BatchState* batch;       // batch-wide counters
     int32_t n_atoms;         // atoms of this system
+};
+static_assert(sizeof(CtlState) % sizeof(uint64_t) == 0, "copied in 64-bit words");
+struct Ctl : CtlState {
+    // Gram matrix of {s of slot q at q, y of slot q at kMaxM + q, g at 2 kMaxM}
+    double gram[kGramDim * kGramDim];
     // workgroups of the running finalize and accept pass that are done (the
     // last one of each goes on with the reduction and sets it back to 0)
     uint32_t fin_ticket, acc_ticket;

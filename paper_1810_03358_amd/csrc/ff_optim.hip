@@ -1,26 +1,50 @@
 // Per-evaluation finalize (gradient gather, norms, energy total) and the
 // optimizer's vector passes: trial point / direction construction and the
-// accept pass (history vectors and their dot products).  A pass that ends in
-// a reduction writes per-workgroup partials; a second kernel with one
-// workgroup per system sums them in a fixed order and runs the decision step.
-// (No workgroup waits for others inside a kernel: on this GPU each XCD has its
-// own L2, and the device-scope fence such a handshake needs writes the L2
-// back every time; the kernel boundary does that once.)
+// accept pass (history vectors and their dot products).  In a pass that ends in
+// a reduction each workgroup leaves partials, and a system's last workgroup sums
+// them in a fixed order and runs the decision step (no workgroup waits for
+// others).
 #include "ff_decide.h"
 
 namespace ff {
 
+// Value of lane l ^ o of every 16 lanes' row (DPP), where the values already
+// repeat with period 2 o: a rotation by o then reads the same as the exchange.
+template <int O>
+__device__ __forceinline__ double row_partner(double v) {
+    constexpr int kCtrl = O == 1 ? 0xB1 /* quad_perm 1 0 3 2 */ : O == 2 ? 0x4E /* quad_perm 2 3 0 1 */
+                                                                : 0x120 + O /* row_ror */;
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, kCtrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), kCtrl, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
 
-// Wavefront sum of a double (xor butterfly).
+// op over a wavefront in the order of an xor butterfly (32, 16, ... 1), every
+// lane receives it: register exchanges instead of twelve trips through the LDS
+// crossbar, since the direction below is a chain of 21 such sums (with the
+// decision on a copy in LDS, an accept pass of 512 atoms and ten pairs takes 16
+// us instead of 22).
+template <typename OP>
+__device__ __forceinline__ double wave_reduce(double v, OP op) {
+    auto halves = [&](auto swap) {
+        const long long b = __double_as_longlong(v);
+        const auto lo = swap((unsigned)b), hi = swap((unsigned)(b >> 32));
+        v = op(__longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])),
+               __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1])));
+    };
+    halves([](unsigned x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+    halves([](unsigned x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    v = op(v, row_partner<8>(v));
+    v = op(v, row_partner<4>(v));
+    v = op(v, row_partner<2>(v));
+    return op(v, row_partner<1>(v));
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, [](double a, double b) { return a + b; });
 }
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
+    return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
 }
 
 // Sum (or max for index 0 if first_is_max) of NV per-thread values over a
@@ -46,21 +70,6 @@ __device__ __forceinline__ void block_reduce(double (&v)[NV], bool first_is_max,
     __syncthreads();
 }
 
-// Fixed-order sum of n doubles by one 256-thread block (result in thread 0).
-__device__ __forceinline__ double block_sum_array(const double* p, int n, bool is_max = false) {
-    double v = is_max ? 0.0 : 0.0;
-    for (int i = threadIdx.x; i < n; i += kFinBlock) v = is_max ? fmax(v, p[i]) : v + p[i];
-    double arr[1] = {v};
-    __shared__ double res;
-    double out[1];
-    block_reduce<1>(arr, is_max, out);
-    if (threadIdx.x == 0) res = out[0];
-    __syncthreads();
-    const double r = res;
-    __syncthreads();
-    return r;
-}
-
 // -------------------------------------------------------- L-BFGS direction
 // Coefficients of the L-BFGS direction r = -H g (Algorithm 3) in the basis
 // {s_0..s_{n-1}, y_0..y_{n-1}, g} of the stored pairs (oldest first) and the
@@ -72,7 +81,7 @@ __device__ __forceinline__ double block_sum_array(const double* p, int n, bool i
 // descent direction (<g, r> < 0) the terms of r and |r| are written to the
 // control block and lb_ready = 1, otherwise lb_ready = -1.  Every thread of
 // the workgroup calls this; hist_n >= 1.
-__device__ void lbfgs_direction_block(Ctl* c) {
+__device__ void lbfgs_direction_block(CtlState* c, const double* gram) {
     __shared__ double gs[kGramDim * kGramDim];
     __shared__ double cs[kGramDim];
     __shared__ int pos[kGramDim];
@@ -83,7 +92,7 @@ __device__ void lbfgs_direction_block(Ctl* c) {
     __syncthreads();
     for (int e = threadIdx.x; e < nb * nb; e += blockDim.x) {
         const int r = e / nb, q = e - r * nb;
-        gs[e] = c->gram[pos[r] * kGramDim + pos[q]];
+        gs[e] = gram[pos[r] * kGramDim + pos[q]];
     }
     __syncthreads();
     if (threadIdx.x >= 64) return;
@@ -188,6 +197,13 @@ __device__ __forceinline__ bool last_workgroup(uint32_t* ticket, int n) {
     return last != 0;
 }
 
+// A control block's state between memory and LDS, by a whole workgroup: the
+// decision step is a chain of small dependent accesses by one thread.
+__device__ __forceinline__ void copy_state(CtlState* to, const CtlState* from) {
+    for (int k = threadIdx.x; k < (int)(sizeof(CtlState) / sizeof(uint64_t)); k += kFinBlock)
+        reinterpret_cast<uint64_t*>(to)[k] = reinterpret_cast<const uint64_t*>(from)[k];
+}
+
 // Pair partials of one 64-atom tile t of I-block `row`, summed over its
 // partial rows in a fixed order.  The tile's rows are the i-side partials
 // of every chunk of its I-block, then the j-side partials of every unit that
@@ -280,6 +296,10 @@ __device__ __forceinline__ double energy_share(const Args& a, const SysInfo& si,
 // energies, which the system's last workgroup adds up.  Grid: every tile of
 // every system
 // (flat, map_fin).
+// (The decision is a call: inlined, it costs the gather of every tile registers
+// and 96 chains of 200-4,000 atoms 1 % of an evaluation.)
+__device__ __attribute__((noinline)) void decide(CtlState* c) { after_eval(c); }
+
 __global__ void __launch_bounds__(kFinBlock) k_finalize(Args a) {
     const Layout& L = a.L;
     const int2 mb = at<int2>(a.ws, L.off_map_fin)[blockIdx.x];
@@ -375,21 +395,28 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(Args a) {
         w[2] += get_partial(red + 4 * b + 2);
         w[3] += get_partial(red + 4 * b + 3);
     }
+    static_assert(sizeof(CtlState) <= sizeof fbv, "the state takes the place of the slots");
+    CtlState& state = *reinterpret_cast<CtlState*>(fbv);
+    if (!a.direct) copy_state(&state, c);
     double gt[4];
     block_reduce<4>(w, true, gt);
-    if (threadIdx.x != 0) return;
-    const double E = gt[3];
     if (a.direct) {
-        if (a.e_out) a.e_out[sys] = E;
-        if (a.g2_out) a.g2_out[sys] = gt[1];
+        if (threadIdx.x == 0) {
+            if (a.e_out) a.e_out[sys] = gt[3];
+            if (a.g2_out) a.g2_out[sys] = gt[1];
+        }
         return;
     }
-    const int tg = c->target;
-    c->e[tg] = E;
-    c->ginf[tg] = gt[0];
-    c->g2[tg] = gt[1];
-    if (want_slope) c->slope = gt[2];
-    after_eval(c);
+    if (threadIdx.x == 0) {
+        const int tg = state.target;
+        state.e[tg] = gt[3];
+        state.ginf[tg] = gt[0];
+        state.g2[tg] = gt[1];
+        if (want_slope) state.slope = gt[2];
+        decide(&state);
+    }
+    __syncthreads();
+    copy_state(c, &state);
 }
 
 // ------------------------------------------------------------------- prepare
@@ -535,13 +562,18 @@ __global__ void __launch_bounds__(kFinBlock) k_accept(Args a) {
         for (int b = 0; b < nbx; ++b) acc += get_partial(red + ((size_t)r * nbx + b) * 6 + q);
         dots[k] = acc;
     }
-    __shared__ int need_dir;
+    __shared__ CtlState state;
+    copy_state(&state, c);
     __syncthreads();
-    if (threadIdx.x == 0) need_dir = accept_update(c, dots) ? 1 : 0;
+    if (method == M_LBFGS) {
+        if (lbfgs_update(&state, c->gram, dots)) lbfgs_direction_block(&state, c->gram);
+    } else if (threadIdx.x == 0) {
+        accept_update(&state, dots);
+    }
     __syncthreads();
-    if (need_dir) lbfgs_direction_block(c);
+    if (threadIdx.x == 0) accept_finish(&state);
     __syncthreads();
-    if (threadIdx.x == 0) accept_finish(c);
+    copy_state(c, &state);
 }
 
 // ---------------------------------------------------------------------- kick
@@ -571,7 +603,7 @@ __global__ void k_kick(Args a, MinParamsDev p, int resume, double* trace, int tr
             need_dir = p.method == M_LBFGS && c->hist_n > 0;
         }
         __syncthreads();
-        if (need_dir) lbfgs_direction_block(c);
+        if (need_dir) lbfgs_direction_block(c, c->gram);
         __syncthreads();
         if (threadIdx.x == 0) begin_iteration(c);
         return;
