@@ -216,6 +216,24 @@ __device__ __forceinline__ void bonded_block(const Args& a, int wg, int prec) {
     block_energy_store<THREADS / 64>(even + odd, at<double>(a.ws, a.L.off_eb) + si.eb0 + m.y, threadIdx.x);
 }
 
+// Pairs of i-atom i with the atoms J0 .. J0 + 63 of a tile that count: bit jj is
+// set if J0 + jj > i and the pair is not excluded.  excl: the atom's near
+// exclusions (bit b: i + 1 + b), far: its far ones in this tile (bit jj).
+// Returned rotated so that bit s belongs to step s of lane `lane`.
+__device__ __forceinline__ uint64_t step_mask(int i, int J0, uint64_t excl, uint64_t far, int lane) {
+    const int sh = i + 1 - J0;               // bit of atom i + 1
+    uint64_t after, ex;
+    if (sh <= 0) {
+        after = ~0ull;
+        ex = -sh < 64 ? excl >> (-sh) : 0ull;
+    } else {
+        after = sh < 64 ? ~0ull << sh : 0ull;
+        ex = sh < 64 ? excl << sh : 0ull;
+    }
+    const uint64_t keep = after & ~ex & ~far;
+    return (keep >> lane) | (keep << ((64 - lane) & 63));
+}
+
 // ---------------------------------------------------------------- FP32 pairs
 
 // i-atoms of one lane: high halves of the coordinates and the per-atom
@@ -258,24 +276,28 @@ __device__ __forceinline__ void close_pair32(const IAtoms32<IPL>& I, int k, floa
     }
 }
 
-template <int IPL, bool MASKED, bool CHECK, bool FAR = false>
+// The 64 steps of a j-tile: at step s lane l takes atom (l + s) mod 64.
+// MASKED: only the pairs of `keep` (step_mask) count; the mask is made once per
+// tile (20 chains of 1,500 atoms: 62.7 us, 71 with the exclusions looked up in
+// every step; two words of 32 steps with a loop each are as fast there and cost
+// 50,000 atoms 1.5 %).
+template <int IPL, bool MASKED, bool CHECK>
 __device__ __forceinline__ void tile32(const float4* __restrict__ s_xq, const float2* __restrict__ s_c,
                                        const float4* __restrict__ s_lo, const float4* __restrict__ s_ilo,
-                                       int lane, int il0, int i0, int J0, const uint64_t* __restrict__ EX,
-                                       const uint64_t* __restrict__ s_far,
+                                       int lane, int il0, const uint64_t (&keep)[IPL],
                                        const IAtoms32<IPL>& I, float (&fx)[IPL], float (&fy)[IPL],
                                        float (&fz)[IPL], double (&gx)[IPL], double (&gy)[IPL],
                                        double (&gz)[IPL], float& fjx, float& fjy, float& fjz,
                                        float& elj, float& ec32, double& e64) {
-    uint64_t excl[IPL];
-    if (MASKED) {
-#pragma unroll
-        for (int k = 0; k < IPL; ++k) excl[k] = EX[i0 + k * 64];
-    }
     // The loop without checks is fetched best when it starts 16 bytes into a
     // 32-byte block: 50,000 atoms take 848 us there and 857-861 us at the other
     // multiples of 8 bytes.
     if (!MASKED && !CHECK) asm volatile(".p2align 5\n.rept 4\ns_nop 0\n.endr");
+    int64_t bits[IPL];                           // the next step's in the sign bit
+    if (MASKED) {
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) bits[k] = (int64_t)__brevll(keep[k]);
+    }
 #pragma unroll kUnroll32<IPL>
     for (int s = 0; s < kTile; ++s) {
         const int js = lane + s;
@@ -288,13 +310,8 @@ __device__ __forceinline__ void tile32(const float4* __restrict__ s_xq, const fl
             float dz = pj.z - I.zh[k];
             float r2 = __fmaf_rn(dz, dz, __fmaf_rn(dy, dy, dx * dx));
             if (MASKED) {
-                const int delta = J0 + (js & (kTile - 1)) - (i0 + k * 64);
-                const unsigned dm1 = (unsigned)(delta - 1);
-                bool ex = dm1 < (unsigned)kExclWindow && ((excl[k] >> (dm1 & 63u)) & 1ull);
-                // far exclusions: this unit's mask of the i-atom, read from LDS
-                // every step (a register copy would raise the kernel's VGPRs)
-                if (FAR) ex = ex || ((s_far[il0 + k * 64] >> (js & (kTile - 1))) & 1ull);
-                r2 = (delta > 0 && !ex) ? r2 : __builtin_inff();
+                r2 = bits[k] < 0 ? r2 : __builtin_inff();
+                bits[k] <<= 1;
             }
             if (CHECK && r2 < kCorrR2)
                 close_pair32<IPL>(I, k, pj, s_lo[js], s_ilo[il0 + k * 64], cj, dx, dy, dz, r2, gx[k], gy[k],
@@ -322,15 +339,33 @@ __device__ __forceinline__ void tile32(const float4* __restrict__ s_xq, const fl
     }
 }
 
-__device__ __forceinline__ float wave_minf(float v) {
+// op over a wavefront, every lane receives it: through the LDS crossbar, which
+// leaves the vector units to the other wavefronts, or (REGS) by register
+// exchanges (permlane swaps, DPP rotations of 16 lanes), which are sooner done
+// (50,000 atoms: 858 us against 889; 512 atoms: 12.6 against 12.1).
+template <bool REGS, typename OP>
+__device__ __forceinline__ float wave_reducef(float v, OP op) {
+    if (!REGS) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
-    return v;
+        for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o, 64));
+        return v;
+    }
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+    v = op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, true)));   // row_ror:8
+    v = op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xF, 0xF, true)));
+    v = op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x122, 0xF, 0xF, true)));
+    return op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x121, 0xF, 0xF, true)));
 }
+template <bool REGS>
+__device__ __forceinline__ float wave_minf(float v) {
+    return wave_reducef<REGS>(v, [](float a, float b) { return fminf(a, b); });
+}
+template <bool REGS>
 __device__ __forceinline__ float wave_maxf(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    return wave_reducef<REGS>(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 __device__ __forceinline__ void split(double v, float& hi, float& lo) {
@@ -363,7 +398,7 @@ k_pair32(Args a) {
     const double* X = eval_coords(a, ch.sys, si);
     constexpr int B = 64 * WAVES * IPL;
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: a scalar register
+    const int wave = IPL == 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const int n = si.n, aoff = si.aoff;
     const float* C12 = at<float>(a.ws, L.off_c12);
     const float* C6 = at<float>(a.ws, L.off_c6);
@@ -386,6 +421,21 @@ k_pair32(Args a) {
     // (kept in LDS for the j-tile staging: registers are at their limit)
     __shared__ double s_org[3];
     double org[3];
+    // With one i-atom per lane, where chunks are one or a few tiles, the first
+    // j-tile's atoms are on their way while the i-atoms are set up (with two
+    // the registers are at their limit).
+    constexpr bool kAhead = IPL == 1;
+    constexpr bool kRegs = WAVES * IPL == 1;     // systems too small to fill the SIMDs
+    double pj[3];
+    float qj = 0.0f;
+    float2 cj = make_float2(0.0f, 0.0f);
+    auto load_tile = [&](int t) {
+        const int j = t * kTile + (int)threadIdx.x;
+        load_pos(X, j - aoff, n, pj);
+        qj = Q[j];
+        cj = make_float2(C12[j], C6[j]);
+    };
+    if (kAhead && threadIdx.x < kTile) load_tile(ch.t_begin);
     load_pos(X, I0 - aoff, n, org);
     if (threadIdx.x == 0) { s_org[0] = org[0]; s_org[1] = org[1]; s_org[2] = org[2]; }
 #pragma unroll
@@ -415,34 +465,31 @@ k_pair32(Args a) {
         ib[2] = fminf(ib[2], I.zh[k]); ib[5] = fmaxf(ib[5], I.zh[k]);
     }
 #pragma unroll
-    for (int c = 0; c < 3; ++c) { ib[c] = wave_minf(ib[c]); ib[3 + c] = wave_maxf(ib[3 + c]); }
+    for (int c = 0; c < 3; ++c) { ib[c] = wave_minf<kRegs>(ib[c]); ib[3 + c] = wave_maxf<kRegs>(ib[3 + c]); }
     __shared__ float s_jbox[6];
     __shared__ float4 s_xq[2 * kTile];
     __shared__ float2 s_c[2 * kTile];
     __shared__ float4 s_lo[2 * kTile];
     __shared__ float s_fj[WAVES][3][kTile];
-    __shared__ uint64_t s_far[HAS_FAR ? B : 1];      // far-exclusion masks of a far unit
     double e64 = 0.0;
     const int t_masked_end = (I0 + B) / kTile + 1;   // tiles that can hold j <= i or exclusions
     for (int t = ch.t_begin; t < ch.t_end; ++t) {
         const int J0 = t * kTile;
         __syncthreads();
         if (threadIdx.x < kTile) {
-            const int j = J0 + threadIdx.x;
-            double p[3];
-            load_pos(X, j - aoff, n, p);
+            if (!kAhead || t > ch.t_begin) load_tile(t);
             float4 h, l;
-            split(p[0] - s_org[0], h.x, l.x);
-            split(p[1] - s_org[1], h.y, l.y);
-            split(p[2] - s_org[2], h.z, l.z);
-            h.w = Q[j];
+            split(pj[0] - s_org[0], h.x, l.x);
+            split(pj[1] - s_org[1], h.y, l.y);
+            split(pj[2] - s_org[2], h.z, l.z);
+            h.w = qj;
             l.w = 0.0f;
-            const float2 c = make_float2(C12[j], C6[j]);
+            const float2 c = cj;
             s_xq[threadIdx.x] = h; s_xq[threadIdx.x + kTile] = h;
             s_lo[threadIdx.x] = l; s_lo[threadIdx.x + kTile] = l;
             s_c[threadIdx.x] = c;  s_c[threadIdx.x + kTile] = c;
-            const float b0 = wave_minf(h.x), b1 = wave_minf(h.y), b2 = wave_minf(h.z);
-            const float b3 = wave_maxf(h.x), b4 = wave_maxf(h.y), b5 = wave_maxf(h.z);
+            const float b0 = wave_minf<kRegs>(h.x), b1 = wave_minf<kRegs>(h.y), b2 = wave_minf<kRegs>(h.z);
+            const float b3 = wave_maxf<kRegs>(h.x), b4 = wave_maxf<kRegs>(h.y), b5 = wave_maxf<kRegs>(h.z);
             if (threadIdx.x == 0) {
                 s_jbox[0] = b0; s_jbox[1] = b1; s_jbox[2] = b2;
                 s_jbox[3] = b3; s_jbox[4] = b4; s_jbox[5] = b5;
@@ -458,22 +505,20 @@ k_pair32(Args a) {
         const float gzb = fmaxf(0.0f, fmaxf(s_jbox[2] - ib[5], ib[2] - s_jbox[5]));
         const bool far = gxb * gxb + gyb * gyb + gzb * gzb >= kCorrR2;
         const int fu = HAS_FAR ? FU[ch.unit + t - ch.t_begin] : -1;
-        if (HAS_FAR && fu >= 0) {
-            // the unit holds excluded pairs more than kExclWindow apart: each
-            // lane copies the masks of its i-atoms (and only reads its own)
+        uint64_t keep[IPL];
+        if ((HAS_FAR && fu >= 0) || t < t_masked_end) {
 #pragma unroll
-            for (int k = 0; k < IPL; ++k) s_far[il0 + k * 64] = FM[(size_t)fu * B + il0 + k * 64];
-            tile32<IPL, true, true, true>(s_xq, s_c, s_lo, s_ilo, lane, il0, i0, J0, EX, s_far, I, fx, fy, fz, gx,
-                                          gy, gz, fjx, fjy, fjz, elj, ec32, e64);
-        } else if (t < t_masked_end)
-            tile32<IPL, true, true>(s_xq, s_c, s_lo, s_ilo, lane, il0, i0, J0, EX, s_far, I, fx, fy, fz, gx, gy, gz,
-                                    fjx, fjy, fjz, elj, ec32, e64);
-        else if (!far)
-            tile32<IPL, false, true>(s_xq, s_c, s_lo, s_ilo, lane, il0, i0, J0, EX, s_far, I, fx, fy, fz, gx, gy, gz,
-                                     fjx, fjy, fjz, elj, ec32, e64);
+            for (int k = 0; k < IPL; ++k)
+                keep[k] = step_mask(i0 + k * 64, J0, EX[i0 + k * 64],
+                                    HAS_FAR && fu >= 0 ? FM[(size_t)fu * B + il0 + k * 64] : 0ull, lane);
+            tile32<IPL, true, true>(s_xq, s_c, s_lo, s_ilo, lane, il0, keep, I, fx, fy, fz, gx, gy, gz, fjx, fjy, fjz,
+                                    elj, ec32, e64);
+        } else if (!far)
+            tile32<IPL, false, true>(s_xq, s_c, s_lo, s_ilo, lane, il0, keep, I, fx, fy, fz, gx, gy, gz, fjx, fjy, fjz,
+                                     elj, ec32, e64);
         else
-            tile32<IPL, false, false>(s_xq, s_c, s_lo, s_ilo, lane, il0, i0, J0, EX, s_far, I, fx, fy, fz, gx, gy, gz,
-                                      fjx, fjy, fjz, elj, ec32, e64);
+            tile32<IPL, false, false>(s_xq, s_c, s_lo, s_ilo, lane, il0, keep, I, fx, fy, fz, gx, gy, gz, fjx, fjy, fjz,
+                                      elj, ec32, e64);
 #pragma unroll
         for (int k = 0; k < IPL; ++k) { gx[k] += fx[k]; gy[k] += fy[k]; gz[k] += fz[k]; }
         e64 += (double)elj * (1.0 / 12.0) + (double)ec32;
@@ -519,24 +564,6 @@ __device__ __forceinline__ double rsqrt_step(double x) {
     double e = fma(-x * y, y, 1.0);
     if (SPECIAL) e = fmin(e, 1.0);
     return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
-// Pairs of i-atom i with the atoms J0 .. J0 + 63 of a tile that count: bit jj is
-// set if J0 + jj > i and the pair is not excluded.  excl: the atom's near
-// exclusions (bit b: i + 1 + b), far: its far ones in this tile (bit jj).
-// Returned rotated so that bit s belongs to step s of lane `lane`.
-__device__ __forceinline__ uint64_t step_mask(int i, int J0, uint64_t excl, uint64_t far, int lane) {
-    const int sh = i + 1 - J0;               // bit of atom i + 1
-    uint64_t after, ex;
-    if (sh <= 0) {
-        after = ~0ull;
-        ex = -sh < 64 ? excl >> (-sh) : 0ull;
-    } else {
-        after = sh < 64 ? ~0ull << sh : 0ull;
-        ex = sh < 64 ? excl << sh : 0ull;
-    }
-    const uint64_t keep = after & ~ex & ~far;
-    return (keep >> lane) | (keep << ((64 - lane) & 63));
 }
 
 // Steps [s0, s1) of a j-tile (multiples of kPartSteps): at step s lane l takes
