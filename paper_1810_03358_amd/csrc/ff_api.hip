@@ -7,9 +7,10 @@
 // build the point (trial / direction / momentum) -> FP32 pair kernel -> FP64
 // pair kernel (each with the bonded terms of the systems that it evaluates) ->
 // finalize (+ decision) -> accept pass (+ decision).  Each cycle advances every
-// unfinished system by one evaluation; work of a system that has nothing to do in a kernel returns at once (its
-// control block says so).  The host replays the graph, one batch of graphs ahead
-// of the reported number of finished systems.
+// unfinished system by one evaluation; work of a system that has nothing to do
+// in a kernel returns at once (its control block says so).  The host replays
+// the graph, one batch of graphs ahead of the reported number of finished
+// systems.
 #include <algorithm>
 #include <utility>
 #include <cstdarg>

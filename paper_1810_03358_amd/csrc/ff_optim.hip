@@ -492,8 +492,7 @@ __global__ void __launch_bounds__(kFinBlock) k_accept(Args a) {
     const int n3 = 3 * si.n;
     const int method = c->p.method;
     const int row = blockIdx.y;
-    // acc_rows is fixed while this pass runs (the reduce kernel changes
-    // hist_n afterwards)
+    // acc_rows is fixed while this pass runs (its last workgroup changes hist_n)
     const int rows = c->acc_rows;
     const bool active = row < rows;
     double* red = at<double>(a.ws, a.L.off_red) + si.red0;
