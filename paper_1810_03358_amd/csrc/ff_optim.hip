@@ -453,6 +453,7 @@ __global__ void __launch_bounds__(kFinBlock) k_prepare(Args a) {
     double di;
     if (pm == PM_DIR_TRIAL || pm == PM_OGM_Y) {
         double r = __dmul_rn(c->term_coef[0], vec(a, c->term_vec[0], si)[i]);
+#pragma unroll 4
         for (int k = 1; k < c->n_terms; ++k) r = __dadd_rn(r, __dmul_rn(c->term_coef[k], vec(a, c->term_vec[k], si)[i]));
         if (c->write_r) vec(a, V_R, si)[i] = r;
         di = __ddiv_rn(r, c->dir_scale);
@@ -509,6 +510,7 @@ __global__ void __launch_bounds__(kFinBlock) k_accept(Args a) {
             const double* src = c->ogm_s_anchor ? vec(a, V_G0 + c->prev_x, si) : vec(a, V_R, si);
             double* S = vec(a, V_R, si);
             const double t = c->ogm_t_next;
+#pragma unroll 4
             for (int i = bx * kFinBlock + threadIdx.x; i < n3; i += stride) {
                 const double sn = __dadd_rn(src[i], __dmul_rn(t, gn[i]));
                 S[i] = sn;
@@ -517,6 +519,7 @@ __global__ void __launch_bounds__(kFinBlock) k_accept(Args a) {
             }
         } else if (method == M_CG) {
             const double* r = vec(a, V_R, si);
+#pragma unroll 4
             for (int i = bx * kFinBlock + threadIdx.x; i < n3; i += stride) {
                 v[0] += gn[i] * go[i];
                 v[1] += gn[i] * r[i];
@@ -525,6 +528,7 @@ __global__ void __launch_bounds__(kFinBlock) k_accept(Args a) {
         } else if (row == 0) {
             double* ss = vec(a, c->spare_s, si);
             double* yy = vec(a, c->spare_y, si);
+#pragma unroll 4
             for (int i = bx * kFinBlock + threadIdx.x; i < n3; i += stride) {
                 const double s = __dsub_rn(xn[i], xo[i]);
                 const double g = gn[i];
@@ -537,6 +541,7 @@ __global__ void __launch_bounds__(kFinBlock) k_accept(Args a) {
         } else {
             const double* S = vec(a, c->hist_s[row - 1], si);
             const double* Y = vec(a, c->hist_y[row - 1], si);
+#pragma unroll 4
             for (int i = bx * kFinBlock + threadIdx.x; i < n3; i += stride) {
                 const double s = __dsub_rn(xn[i], xo[i]);
                 const double g = gn[i];
