@@ -177,7 +177,7 @@ int32_t ff_batch_size(const ff_ctx *ctx);
  * I-blocks of `block` atoms against j-tiles of 64 atoms, and one workgroup
  * walks a chunk of consecutive j-tiles of one I-block: `chunk` tiles in the
  * FP32 kernel, `chunk64` in the FP64 kernel (each has its own chunk table).
- * With FP32 chunks longer than one tile, the last sixteenth of each I-block's
+ * With chunks longer than one tile, the last sixteenth of each I-block's
  * j-tiles (at least one) goes to one-tile chunks that end the launch, so that
  * it drains on short workgroups.  FP64 chunks of one tile are cut into halves
  * or quarters of a tile in systems too small to fill the chip with whole ones.

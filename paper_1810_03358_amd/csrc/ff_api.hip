@@ -156,6 +156,11 @@ static int fp64_split(int chunk, long long units, int waves) {
     return split;
 }
 
+// FP64 chunks of an I-block with T j-tiles.
+static int row_chunks64(const Layout& L, int T) {
+    return L.split < kParts ? T * (kParts / L.split) : row_split(T, L.chunk[1]).count();
+}
+
 static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout& L, SysInfo* sys, FarTmp& ft,
                         int32_t cfg_req = -1, int32_t chunk_req = 0, int32_t chunk64_req = 0,
                         bool energy_only = false) {
@@ -179,9 +184,9 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
     // batches, whose small systems larger blocks would pad; 256 with two atoms
     // per lane in FP32 and four in FP64 above.  The FP64 chunks grow with the
     // system: one j-tile up to 14,500 (13,000 atoms: 127.0 us, 133.4 with two),
-    // two up to 40,000 (30,000 atoms: 534 us, 558 with one, 536 with four), four
-    // above (50,000 atoms: 1,397 us, 1,428 with two, 1,437 with eight); batches
-    // one (96 chains of 200-4,000 atoms: 208.8 us, 215.5 with four).  The FP32
+    // two up to 40,000 (34,000 atoms: 684 us, 696 with four), six above (45,000
+    // atoms: 1,142 us, 1,174 with four, 1,187 with eight; 50,000 atoms: 1,415,
+    // 1,446 with four, 1,411 with eight); batches one (96 chains of 200-4,000 atoms: 208.8 us, 215.5 with four).  The FP32
     // kernel gains from two j-tiles only above 32,768 atoms, and from four in
     // batches.
     auto pick = [&](int cfg, int c32, int c64) { L.cfg = cfg; L.chunk[0] = c32; L.chunk[1] = c64; };
@@ -192,7 +197,7 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
     else if (n_max < 20000) pick(9, 1, 2);
     else if (n_max < 32768) pick(8, 1, 2);
     else if (n_max <= 40000) pick(8, 2, 2);
-    else pick(8, 2, 4);
+    else pick(8, 2, 6);
     if (cfg_req >= 0) {
         if (chunk64_req == 0) chunk64_req = chunk_req;
         if (cfg_req >= kNumTileConfigs || chunk_req < 1 || chunk_req > kMaxChunk || chunk64_req < 1 ||
@@ -227,7 +232,7 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
             const int t0 = b * L.block / kTile;
             units += nt - t0;
             chunks[0] += row_split(nt - t0, L.chunk[0]).count();
-            chunks[1] += ((nt - t0) * kParts + L.split - 1) / L.split;
+            chunks[1] += row_chunks64(L, nt - t0);
         }
         for (int p = 0; p < 2; ++p) si.n_chunks[p] = chunks[p] - si.chunk0[p];
         si.n_bonds = s[k].n_bonds;
@@ -442,7 +447,7 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
             r.chunk_start[0] = slot[0];
             r.chunk_start[1] = slot[1];
             r.n_chunks[0] = row_split(T, L.chunk[0]).count();
-            r.n_chunks[1] = (T * kParts + L.split - 1) / L.split;
+            r.n_chunks[1] = row_chunks64(L, T);
             slot[0] += r.n_chunks[0];
             slot[1] += r.n_chunks[1];
             unit += T;
@@ -450,9 +455,10 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
     }
     if (slot[0] != L.n_chunks[0] || slot[1] != L.n_chunks[1] || unit != L.n_units)
         return fail(FF_ERR_ARG, "internal: tile table size mismatch");
-    {
-        ChunkInfo* chunks = at<ChunkInfo>(img, L.off_chunks[0]);
-        const int c_len = L.chunk[0];
+    for (int tab = 0; tab < 2; ++tab) {
+        ChunkInfo* chunks = at<ChunkInfo>(img, L.off_chunks[tab]);
+        const bool cut = tab == 1 && L.split < kParts;       // chunks are parts of a tile
+        const int c_len = L.chunk[tab], per = cut ? kParts / L.split : 1;
         int nch = 0;
         for (int pass = 0; pass < 3; ++pass) {
             for (int k = 0; k < n_sys; ++k) {
@@ -461,59 +467,31 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
                 for (int row = si.row0; row < si.row0 + si.nb; ++row) {
                     const RowInfo& ri = rows[row];
                     const RowSplit sp = row_split(t_end - ri.t0, c_len);
-                    int t = ri.t0, q = ri.chunk_start[0];
+                    int t = ri.t0, q = ri.chunk_start[tab];
                     auto emit = [&](int len, int in_pass) {
-                        if (in_pass == pass) {
+                        for (int part = 0; part < per; ++part, ++q) {
+                            if (in_pass != pass) continue;
                             ChunkInfo& c = chunks[nch++];
                             c.row = row;
                             c.t_begin = t;
                             c.t_end = t + len;
-                            c.j_row = c.unit = ri.unit_start + (t - ri.t0);
+                            c.unit = ri.unit_start + (t - ri.t0);
+                            c.j_row = c.unit * per + part;
                             c.sys = k;
                             c.slot = q;
-                            c.steps = kTile << 8;
+                            c.steps = part * (kTile / per) | ((part + 1) * (kTile / per)) << 8;
                         }
                         t += len;
-                        ++q;
                     };
                     for (int i = 0; i < sp.full; ++i) emit(c_len, c_len == 1 ? 2 : 0);
                     if (sp.rem > 0) emit(sp.rem, sp.rem == 1 ? 2 : 1);
                     for (int i = 0; i < sp.tail; ++i) emit(1, 2);
-                    if (t != t_end || q != ri.chunk_start[0] + ri.n_chunks[0])
+                    if (t != t_end || q != ri.chunk_start[tab] + ri.n_chunks[tab])
                         return fail(FF_ERR_ARG, "internal: chunk split mismatch");
                 }
             }
         }
-        if (nch != L.n_chunks[0]) return fail(FF_ERR_ARG, "internal: chunk table size mismatch");
-    }
-    {
-        // FP64: full-length chunks first, then each I-block's shorter last one
-        ChunkInfo* chunks = at<ChunkInfo>(img, L.off_chunks[1]);
-        int nch = 0;
-        for (int pass = 0; pass < 2; ++pass)
-            for (int k = 0; k < n_sys; ++k) {
-                const SysInfo& si = sys[k];
-                const int t_end = si.aoff / kTile + si.np / kTile;
-                for (int row = si.row0; row < si.row0 + si.nb; ++row) {
-                    const RowInfo& ri = rows[row];
-                    const int parts = (t_end - ri.t0) * kParts;
-                    for (int c = 0; c < ri.n_chunks[1]; ++c) {
-                        const int e0 = c * L.split, e1 = std::min(parts, e0 + L.split);
-                        if ((e1 - e0 == L.split) != (pass == 0)) continue;
-                        ChunkInfo& o = chunks[nch++];
-                        const int k0 = e0 / kParts, k1 = (e1 - 1) / kParts;
-                        o.row = row;
-                        o.t_begin = ri.t0 + k0;
-                        o.t_end = ri.t0 + k1 + 1;
-                        o.unit = ri.unit_start + k0;
-                        o.j_row = o.unit * unit_rows(L.split) + (L.split < kParts ? c % unit_rows(L.split) : 0);
-                        o.sys = k;
-                        o.slot = ri.chunk_start[1] + c;
-                        o.steps = (e0 - k0 * kParts) * kPartSteps | (e1 - k1 * kParts) * kPartSteps << 8;
-                    }
-                }
-            }
-        if (nch != L.n_chunks[1]) return fail(FF_ERR_ARG, "internal: chunk table size mismatch");
+        if (nch != L.n_chunks[tab]) return fail(FF_ERR_ARG, "internal: chunk table size mismatch");
     }
     // bonded topology (local atom indices) and parameters
     int* bond = at<int>(img, L.off_bond);
