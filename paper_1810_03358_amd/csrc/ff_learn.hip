@@ -318,7 +318,8 @@ __device__ void neighbor_rows(const double* __restrict__ xyz, const double* __re
 #pragma unroll
         for (int k = 0; k < A; ++k) {
             const double r = sqrt(limit[k]) + 2.0 * sqrt(ro[k]);
-            bound[k] = (float)(limit[k] - ro[k] + 0x1p-18 * (r * r)) + 0x1p-100f;      // (+: FP32 underflow)
+            // (+: FP32 underflow; beyond 2^60 squares may exceed FP32, and every candidate passes)
+            bound[k] = r < 0x1p60 ? (float)(limit[k] - ro[k] + 0x1p-18 * (r * r)) + 0x1p-100f : __builtin_inff();
         }
     };
     // candidate c is atom (start + c) mod n_c: the first tile lies around the

@@ -1,0 +1,46 @@
+"""Features of the learned start for points and arrays that ordinary chains do
+not have, exactly as the oracle defines them."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import learn as OL
+from paper_1810_03358_amd import learn as L
+from tests.systems import make_system
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _system(x, seed):
+    n, rng = len(x), np.random.default_rng(seed)
+    return make_system(x, q=rng.uniform(-0.5, 0.5, n), sigma=rng.uniform(3, 4, n), eps=rng.uniform(0.05, 0.2, n))
+
+
+def _oracle(s):
+    return OL.features(s["x"], s["q"], s["sigma"], s["eps"], [0, s["n_atoms"]])
+
+
+# squares of these distances are finite in FP64 and, above about 1.8e19, not in
+# FP32, in which the search makes its first pass
+@pytest.mark.parametrize("far", [1e15, 1e18, 1e19, 1e20, 1e25, 1e30])
+@pytest.mark.parametrize("kind", ["first", "third", "every other", "halves"])
+def test_far_apart_atoms_keep_their_neighbours(far, kind):
+    """More atoms than one tile of the search (256); `far` away lie the first or
+    third atom of some groups of four (which one wavefront searches), or a
+    cluster of half of the atoms: every other one, or the second half and atom 1
+    (whose neighbours then lie in tiles that hold none for atom 0)."""
+    n, rng = 1030 if kind == "halves" else 600, np.random.default_rng(3)
+    x = rng.normal(scale=8.0, size=(n, 3))
+    if kind in ("every other", "halves"):
+        at = np.arange(1, n, 2) if kind == "every other" else np.r_[1, 512:n]
+        x[at] = far * np.array([1.0, -0.5, 0.25]) + rng.normal(scale=far * 1e-12 + 8.0, size=(len(at), 3))
+    else:
+        at = np.arange(0 if kind == "first" else 2, n, 40)
+        x[at] = far * (1.0 + np.arange(len(at))[:, None]) * np.array([1.0, 0.5, -0.25])
+    s = _system(x, 4)
+    print(f"features far={far} {kind}", flush=True)
+    f, nb = L.features(L.SystemArrays([s], DEV), torch.tensor(x, device=DEV), want_neighbors=True)
+    fo, nbo = _oracle(s)
+    np.testing.assert_array_equal(nb.cpu().numpy(), nbo)
+    np.testing.assert_array_equal(f.cpu().numpy().view(np.uint16), fo)
