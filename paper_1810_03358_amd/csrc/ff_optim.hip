@@ -179,13 +179,16 @@ __device__ __forceinline__ double get_partial(const double* p) {
 
 // True in the last of a pass's n workgroups to get here (all threads; thread 0
 // has put the workgroup's partials before).  It goes on with the reduction,
-// instead of a launch of its own.  The partials are in memory once their
+// instead of a launch of its own.  No workgroup counts before all of its
+// wavefronts are here: the last one rewrites the control block that they read
+// on their way.  The partials are in memory once their
 // stores are acknowledged, so the counter needs no release, which would write
 // back the XCD's whole L2 from every workgroup.  FP64 evaluations with the
 // launch, with the last workgroup, and with a release: 512 atoms 17.0, 16.0,
 // 15.8 us; 96 chains of 200-4,000 atoms 205, 206, 248 us.
 __device__ __forceinline__ bool last_workgroup(uint32_t* ticket, int n) {
     __shared__ int last;
+    __syncthreads();
     if (threadIdx.x == 0) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
@@ -493,7 +496,7 @@ __global__ void __launch_bounds__(kFinBlock) k_accept(Args a) {
     const int n3 = 3 * si.n;
     const int method = c->p.method;
     const int row = blockIdx.y;
-    // acc_rows is fixed while this pass runs (its last workgroup changes hist_n)
+    // the control block is fixed until the pass's last workgroup is here
     const int rows = c->acc_rows;
     const bool active = row < rows;
     double* red = at<double>(a.ws, a.L.off_red) + si.red0;
