@@ -163,7 +163,9 @@ struct Ctl : CtlState {
     // Gram matrix of {s of slot q at q, y of slot q at kMaxM + q, g at 2 kMaxM}
     double gram[kGramDim * kGramDim];
     // workgroups of the running finalize and accept pass that are done (the
-    // last one of each goes on with the reduction and sets it back to 0)
+    // last one of each goes on with the reduction and sets it back to 0; each
+    // evaluation's first bonded block and the start of a minimization do so
+    // too, so that a count that overlapping calls left behind ends with them)
     uint32_t fin_ticket, acc_ticket;
 };
 

@@ -589,6 +589,7 @@ __global__ void __launch_bounds__(kFinBlock) k_accept(Args a) {
 __global__ void k_kick(Args a, MinParamsDev p, int resume, double* trace, int trace_cap) {
     const int sys = blockIdx.x;
     Ctl* c = ctl_at(a, sys);
+    if (threadIdx.x == 0) c->fin_ticket = c->acc_ticket = 0u;
     if (resume) {
         // continue where the previous call stopped; the L-BFGS direction is
         // recomputed from the stored pairs exactly as after an accept

@@ -202,6 +202,7 @@ __device__ __forceinline__ void block_energy_store(double e, double* out, int ti
 template <int THREADS>
 __device__ __forceinline__ void bonded_block(const Args& a, int wg, int prec) {
     const int2 m = at<int2>(a.ws, a.L.off_map_bonded)[wg];
+    if (m.y == 0 && threadIdx.x == 0) ctl_at(a, m.x)->fin_ticket = 0u;
     if (!eval_active(a, m.x, prec)) return;
     const SysInfo si = sys_info(a)[m.x];
     const double* X = eval_coords(a, m.x, si);

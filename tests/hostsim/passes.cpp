@@ -93,11 +93,26 @@ void accept_order(const char* name, int method, int bx, int rows) {
            "FAILED: not one decision");
 }
 
+// Counts that something left behind do not outlive the start of a minimization.
+void kick_counts(const char* name, int resume) {
+    Fixture f(1, 2);
+    f.kick(M_GD);
+    f.accept();
+    f.c->fin_ticket = 3;
+    f.c->acc_ticket = 1;
+    MinParamsDev p = f.c->p;
+    Group g([&] { k_kick(f.a, p, resume, nullptr, 0); }, dim3(0), dim3(1), kFinBlock);
+    g.finish();
+    result(name, f.c->fin_ticket == 0 && f.c->acc_ticket == 0, "FAILED: counts are kept");
+}
+
 }  // namespace
 
 int main() {
     accept_order("accept_gd", M_GD, 1, 2);
     accept_order("accept_hb", M_HB, 1, 11);
     accept_order("accept_fgm", M_FGM, 3, 5);
+    kick_counts("kick_counts", 0);
+    kick_counts("resume_counts", 1);
     return 0;
 }

@@ -24,3 +24,8 @@ def lines(tmp_path_factory):
 def test_workgroups_without_a_product_row_stay_whole(lines, name):
     got = [text for n, text in lines if n == name]
     assert got == ["ok", "ok"], got
+
+
+@pytest.mark.parametrize("name", ["kick_counts", "resume_counts"])
+def test_a_minimization_starts_its_counts_at_zero(lines, name):
+    assert [text for n, text in lines if n == name] == ["ok"]
