@@ -397,8 +397,9 @@ __device__ void neighbor_rows(const double* __restrict__ xyz, const double* __re
         if (step + 1 < n_tiles) scan(step + 1, vb);
     }
     if (waiting[0] | waiting[1] | waiting[2] | waiting[3]) merge();
-    // row k writes atom k's row into LDS; it is stored as 32-bit words but for
-    // the entries of the atom's place, which the centroid workgroup writes
+    // row k writes atom k's row into LDS; it is stored as 32-bit words (where
+    // the array is aligned to them) but for the entries of the atom's place,
+    // which the centroid workgroup writes
     uint16_t* rows = rowbuf + wave * A * FF_LEARN_FEATURES;
     const int i = a0 + wave * A + row;
     if (i <= last) {
@@ -429,13 +430,18 @@ __device__ void neighbor_rows(const double* __restrict__ xyz, const double* __re
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const bool words = (uintptr_t)feat % 4 == 0;
     for (int k = 0; k < A && a0 + wave * A + k <= last; ++k) {
         const uint16_t* r = rows + k * FF_LEARN_FEATURES;
         uint16_t* f = feat + (size_t)(a0 + wave * A + k) * FF_LEARN_FEATURES;
         constexpr int w_lo = kPlace / 2, w_hi = (kPlace + 4) / 2;   // first and last word shared with the place
-        if (lane < w_lo || lane > w_hi) ((uint32_t*)f)[lane] = ((const uint32_t*)r)[lane];
-        else if (lane == w_lo) f[2 * w_lo] = r[2 * w_lo];
-        else if (lane == w_hi) f[2 * w_hi + 1] = r[2 * w_hi + 1];
+        const bool both = lane < w_lo || lane > w_hi;
+        if (both && words) {
+            ((uint32_t*)f)[lane] = ((const uint32_t*)r)[lane];
+            continue;
+        }
+        if (both || lane == w_lo) f[2 * lane] = r[2 * lane];
+        if (both || lane == w_hi) f[2 * lane + 1] = r[2 * lane + 1];
     }
 }
 

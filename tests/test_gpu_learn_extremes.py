@@ -1,11 +1,15 @@
 """Features of the learned start for points and arrays that ordinary chains do
 not have, exactly as the oracle defines them."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
 from oracle import learn as OL
+from paper_1810_03358_amd import _native as N
 from paper_1810_03358_amd import learn as L
+from synth import chain_system
 from tests.systems import make_system
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +48,23 @@ def test_far_apart_atoms_keep_their_neighbours(far, kind):
     fo, nbo = _oracle(s)
     np.testing.assert_array_equal(nb.cpu().numpy(), nbo)
     np.testing.assert_array_equal(f.cpu().numpy().view(np.uint16), fo)
+
+
+@pytest.mark.parametrize("shift", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [1, 15, 17, 300])
+def test_features_go_to_any_16_bit_address(n, shift):
+    """The output array may begin at any multiple of two bytes; nothing before or
+    behind it is written."""
+    s = chain_system(n, 8)
+    sa = L.SystemArrays([s], DEV)
+    x = torch.tensor(s["x"], dtype=torch.float64, device=DEV).contiguous()
+    buf = torch.full((n * L.FEATURES + 8,), 0x1234, dtype=torch.int16, device=DEV)
+    print(f"features n={n} at {2 * shift} bytes", flush=True)
+    p = lambda t, skip=0: C.c_void_p(t.data_ptr() + skip)  # noqa: E731
+    assert N.load().ff_learn_features(1, n, p(x), p(sa.q), p(sa.sigma), p(sa.eps), p(sa.sys_first), p(sa.atom_sys),
+                                      p(buf, 2 * shift), None, C.c_void_p(0)) == 0
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy().view(np.uint16)
+    end = shift + n * L.FEATURES
+    np.testing.assert_array_equal(got[shift:end].reshape(n, L.FEATURES), _oracle(s)[0])
+    assert (got[:shift] == 0x1234).all() and (got[end:] == 0x1234).all()
