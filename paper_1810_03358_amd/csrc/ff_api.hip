@@ -458,7 +458,7 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
     for (int tab = 0; tab < 2; ++tab) {
         ChunkInfo* chunks = at<ChunkInfo>(img, L.off_chunks[tab]);
         const bool cut = tab == 1 && L.split < kParts;       // chunks are parts of a tile
-        const int c_len = L.chunk[tab], per = cut ? kParts / L.split : 1;
+        const int c_len = L.chunk[tab], per = cut ? kParts / L.split : 1, steps = kTile / per;
         int nch = 0;
         for (int pass = 0; pass < 3; ++pass) {
             for (int k = 0; k < n_sys; ++k) {
@@ -467,25 +467,25 @@ static ff_status pack_static(const ff_system* systems, int32_t n_sys, const Layo
                 for (int row = si.row0; row < si.row0 + si.nb; ++row) {
                     const RowInfo& ri = rows[row];
                     const RowSplit sp = row_split(t_end - ri.t0, c_len);
+                    const int unit0 = ri.unit_start - ri.t0;
                     int t = ri.t0, q = ri.chunk_start[tab];
-                    auto emit = [&](int len, int in_pass) {
-                        for (int part = 0; part < per; ++part, ++q) {
-                            if (in_pass != pass) continue;
-                            ChunkInfo& c = chunks[nch++];
-                            c.row = row;
-                            c.t_begin = t;
-                            c.t_end = t + len;
-                            c.unit = ri.unit_start + (t - ri.t0);
-                            c.j_row = c.unit * per + part;
-                            c.sys = k;
-                            c.slot = q;
-                            c.steps = part * (kTile / per) | ((part + 1) * (kTile / per)) << 8;
+                    const struct { int count, len, pass; } runs[3] = {
+                        {sp.full, c_len, c_len == 1 ? 2 : 0},
+                        {sp.rem > 0 ? 1 : 0, sp.rem, sp.rem == 1 ? 2 : 1},
+                        {sp.tail, 1, 2}};
+                    for (const auto& run : runs) {
+                        const int n = run.count * per;
+                        if (run.pass == pass) {
+                            for (int i = 0; i < n; ++i) {
+                                const int u = per == 1 ? i : i / per, part = i - u * per, tb = t + u * run.len;
+                                chunks[nch + i] = {row, tb, tb + run.len, (unit0 + tb) * per + part, k, q + i, unit0 + tb,
+                                                   part * steps | ((part + 1) * steps) << 8};
+                            }
+                            nch += n;
                         }
-                        t += len;
-                    };
-                    for (int i = 0; i < sp.full; ++i) emit(c_len, c_len == 1 ? 2 : 0);
-                    if (sp.rem > 0) emit(sp.rem, sp.rem == 1 ? 2 : 1);
-                    for (int i = 0; i < sp.tail; ++i) emit(1, 2);
+                        t += run.count * run.len;
+                        q += n;
+                    }
                     if (t != t_end || q != ri.chunk_start[tab] + ri.n_chunks[tab])
                         return fail(FF_ERR_ARG, "internal: chunk split mismatch");
                 }
