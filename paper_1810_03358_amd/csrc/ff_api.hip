@@ -156,6 +156,16 @@ static int fp64_split(int chunk, long long units, int waves) {
     return split;
 }
 
+// Pairs of an I-block of `block` atoms and a j-tile of its system.
+static long long count_units(const ff_system* s, int32_t n_sys, int block) {
+    long long units = 0;
+    for (int k = 0; k < n_sys; ++k) {
+        const long long nb = (s[k].n_atoms + block - 1) / block;
+        units += nb * (nb + 1) / 2 * (block / kTile);
+    }
+    return units;
+}
+
 // FP64 chunks of an I-block with T j-tiles.
 static int row_chunks64(const Layout& L, int T) {
     return L.split < kParts ? T * (kParts / L.split) : row_split(T, L.chunk[1]).count();
@@ -186,11 +196,16 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
     // system: one j-tile up to 14,500 (13,000 atoms: 127.0 us, 133.4 with two),
     // two up to 40,000 (34,000 atoms: 684 us, 696 with four), six above (45,000
     // atoms: 1,142 us, 1,174 with four, 1,187 with eight; 50,000 atoms: 1,415,
-    // 1,446 with four, 1,411 with eight); batches one (96 chains of 200-4,000 atoms: 208.8 us, 215.5 with four).  The FP32
-    // kernel gains from two j-tiles only above 32,768 atoms, and from four in
-    // batches.
+    // 1,446 with four, 1,411 with eight).
+    // Batches take one-tile FP64 chunks until the tiles themselves fill the chip
+    // several times over (128-atom blocks; 100 chains of 1,000 atoms, 8,000 tiles:
+    // 126 us, 147 with four), then four, which set up and store less (100
+    // chains of 4,000 atoms, 106,000 tiles: 1,134 us with one, 1,075 with four,
+    // and 16 % less workspace); between 16,000 and 24,000 tiles the two are equal.
+    // The FP32 kernel gains from two j-tiles only above 32,768 atoms, and from
+    // four in batches.
     auto pick = [&](int cfg, int c32, int c64) { L.cfg = cfg; L.chunk[0] = c32; L.chunk[1] = c64; };
-    if (n_sys > 1) pick(9, 4, 1);
+    if (n_sys > 1) pick(9, 4, count_units(s, n_sys, 128) < 20000 ? 1 : 4);
     else if (n_max <= 1024) pick(0, 1, 1);
     else if (n_max < 12288) pick(1, 1, 1);
     else if (n_max <= 14500) pick(9, 1, 1);
@@ -206,12 +221,7 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
         pick(cfg_req, chunk_req, chunk64_req);
     }
     L.block = kTileConfigs[L.cfg].block;
-    long long n_units = 0;
-    for (int k = 0; k < n_sys; ++k) {
-        const long long nb = (s[k].n_atoms + L.block - 1) / L.block;
-        n_units += nb * (nb + 1) / 2 * (L.block / kTile);
-    }
-    L.split = fp64_split(L.chunk[1], n_units, kTileConfigs[L.cfg].waves64);
+    L.split = fp64_split(L.chunk[1], count_units(s, n_sys, L.block), kTileConfigs[L.cfg].waves64);
     int aoff = 0, uoff = 0, units = 0, nbd = 0, nag = 0, ndh = 0, ebo = 0;
     int chunks[2] = {0, 0};
     size_t red = 0;
