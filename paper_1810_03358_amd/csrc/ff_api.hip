@@ -188,15 +188,15 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
     if (ft.cap < far_capacity(s, n_sys)) return false;
     L.n_sys = n_sys;
     // defaults from sweeps of whole FP32 and FP64 evaluations on MI355X (300 to
-    // 50,000 atoms and batches, configurations x chunk lengths, per precision).
+    // 120,000 atoms and batches, configurations x chunk lengths, per precision).
     // Blocks: 64 atoms up to 1,024; 256 with one atom per lane up to 12,288
     // (enough workgroups to fill the chip); 128 with two up to 20,000 and in
     // batches, whose small systems larger blocks would pad; 256 with two atoms
     // per lane in FP32 and four in FP64 above.  The FP64 chunks grow with the
     // system: one j-tile up to 14,500 (13,000 atoms: 127.0 us, 133.4 with two),
-    // two up to 40,000 (34,000 atoms: 684 us, 696 with four), six above (45,000
-    // atoms: 1,142 us, 1,174 with four, 1,187 with eight; 50,000 atoms: 1,415,
-    // 1,446 with four, 1,411 with eight).
+    // two up to 40,000 (34,000 atoms: 684 us, 696 with four), six below 50,000
+    // (45,000 atoms: 1,111 us, 1,128 with four, 1,144 with eight), eight above
+    // (50,000 atoms: 1,363 us, 1,367 with six; 55,000: 1,634 and 1,678).
     // Batches take one-tile FP64 chunks until the tiles themselves fill the chip
     // several times over (128-atom blocks; 100 chains of 1,000 atoms, 8,000 tiles:
     // 126 us, 147 with four), then four, which set up and store less (100
@@ -212,7 +212,8 @@ static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout
     else if (n_max < 20000) pick(9, 1, 2);
     else if (n_max < 32768) pick(8, 1, 2);
     else if (n_max <= 40000) pick(8, 2, 2);
-    else pick(8, 2, 6);
+    else if (n_max < 50000) pick(8, 2, 6);
+    else pick(8, 2, 8);
     if (cfg_req >= 0) {
         if (chunk64_req == 0) chunk64_req = chunk_req;
         if (cfg_req >= kNumTileConfigs || chunk_req < 1 || chunk_req > kMaxChunk || chunk64_req < 1 ||

@@ -31,7 +31,7 @@ def _bytes(hosts, tiling=None):
 @pytest.mark.parametrize("n,tiling", [
     (1024, (0, 1, 1)), (1025, (1, 1, 1)), (12287, (1, 1, 1)), (12288, (9, 1, 1)), (14500, (9, 1, 1)),
     (14501, (9, 1, 2)), (19999, (9, 1, 2)), (20000, (8, 1, 2)), (32767, (8, 1, 2)), (32768, (8, 2, 2)),
-    (40000, (8, 2, 2)), (40001, (8, 2, 6)), (49999, (8, 2, 6))])
+    (40000, (8, 2, 2)), (40001, (8, 2, 6)), (49999, (8, 2, 6)), (50000, (8, 2, 8)), (60000, (8, 2, 8))])
 def test_single_systems(chains, n, tiling):
     want = _bytes([chains(n)], tiling)
     assert want > 0 and _bytes([chains(n)]) == want
