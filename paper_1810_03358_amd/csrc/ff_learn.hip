@@ -36,8 +36,9 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
 // FF_LEARN_FEATURES.  Each value is rounded FP64 -> FP32 -> BF16.
 //
 // One launch of two kinds of workgroups that write disjoint bytes:
-//  - one per system sums its coordinates in atom order and writes the three
-//    offsets and their length of every row (centroid_rows);
+//  - one per system or group of small systems sums coordinates in atom order and
+//    writes the three offsets and their length of every row (centroid_rows,
+//    centroid_group);
 //  - one per 16 atoms, each of its wavefronts searching the neighbours of four
 //    (neighbor_rows).
 constexpr int kPlace = 3 + 7 * FF_LEARN_NEIGHBORS;   // first entry of an atom's place in its system
@@ -161,18 +162,18 @@ __device__ void ordered_sum(const double* __restrict__ x, int n, double (*tile)[
     for (int c = 0; c < 3; ++c) sum[c] = tile[0][c];
 }
 
-// Place entries of the rows of system [j0, j1), from its coordinate sums.
-// With err > 0 the sums may be off by that much from the ordered ones: the
+// Place entries of the rows first, first + stride, ... of a system of n atoms, from
+// its coordinate sums.  With err > 0 the sums may be off by that much from the ordered ones: the
 // return value says whether an entry of this thread's rows could then round
 // to another BF16 value.
-__device__ bool place_rows(const double* __restrict__ x, int n, const double (&sum)[3], double err,
-                           uint16_t* __restrict__ feat) {
+__device__ __forceinline__ bool place_rows(const double* __restrict__ x, int n, const double (&sum)[3], double err,
+                           uint16_t* __restrict__ feat, int first = threadIdx.x, int stride = 256) {
 #pragma clang fp contract(off)
     const double nd = (double)n;
     const double c0 = sum[0] / nd, c1 = sum[1] / nd, c2 = sum[2] / nd;
     bool unsure = false;
 #pragma unroll 4
-    for (int a = threadIdx.x; a < n; a += 256) {
+    for (int a = first; a < n; a += stride) {
         const double px = x[3 * (size_t)a], py = x[3 * (size_t)a + 1], pz = x[3 * (size_t)a + 2];
         const double cx = px - c0, cy = py - c1, cz = pz - c2;
         const double v[4] = {cx / 16.0, cy / 16.0, cz / 16.0, sqrt(cx * cx + cy * cy + cz * cz) / 16.0};
@@ -198,7 +199,7 @@ __device__ bool place_rows(const double* __restrict__ x, int n, const double (&s
 // the exact sum (u = 2^-53), so they differ by less than err = n 2^-51 sum|x|.
 // Where every entry rounds alike over that range the rows hold what the
 // ordered sum gives; else (some 1e-3 of 10,000-atom systems) it is formed.
-__device__ void centroid_rows(const double* __restrict__ xyz, int j0, int j1, uint16_t* __restrict__ feat,
+__device__ __forceinline__ void centroid_rows(const double* __restrict__ xyz, int j0, int j1, uint16_t* __restrict__ feat,
                               double (*tile)[3 * kKnnTile]) {
 #pragma clang fp contract(off)
     const int t = threadIdx.x, n = j1 - j0, n_el = 3 * n;
@@ -228,6 +229,41 @@ __device__ void centroid_rows(const double* __restrict__ xyz, int j0, int j1, ui
     place_rows(x, n, sum, 0.0, rows);
 }
 
+// The same for a system of at most W atoms by W lanes of a wavefront (n and j0
+// may differ between the wavefront's groups of W): a lane holds an atom, and the
+// sum is formed in order.
+template <int W>
+__device__ __forceinline__ void centroid_lanes(const double* __restrict__ xyz, int j0, int n, uint16_t* __restrict__ feat) {
+    const int l = threadIdx.x & (W - 1);
+    double p[3] = {0.0, 0.0, 0.0}, sum[3] = {0.0, 0.0, 0.0};
+    if (l < n)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) p[c] = xyz[3 * (size_t)(j0 + l) + c];
+    for (int a = 0; __any(a < n); ++a)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double v = W == 64 ? lane_value(p[c], a) : __shfl(p[c], a, W);
+            if (a < n) sum[c] += v;
+        }
+    if (n > 0) place_rows(xyz + 3 * (size_t)j0, n, sum, 0.0, feat + (size_t)j0 * FF_LEARN_FEATURES, l, W);
+}
+
+// Systems [s0, s0 + kGroup) by one workgroup: 16 lanes, a wavefront or the whole
+// workgroup for each, as their sizes ask.
+constexpr int kGroup = 16;
+__device__ __forceinline__ void centroid_group(const double* __restrict__ xyz, const int32_t* __restrict__ sys_first,
+                                               int s0, int n_sys, uint16_t* __restrict__ feat,
+                                               double (*tile)[3 * kKnnTile]) {
+    auto first = [&](int s) { return s < n_sys ? sys_first[s] : 0; };
+    auto size = [&](int s) { return s < n_sys ? sys_first[s + 1] - sys_first[s] : 0; };
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), own = s0 + (threadIdx.x >> 4);
+    centroid_lanes<16>(xyz, first(own), size(own) <= 16 ? size(own) : 0, feat);
+    for (int s = s0 + 4 * wave; s < s0 + 4 * wave + 4; ++s)
+        if (size(s) > 16 && size(s) <= 64) centroid_lanes<64>(xyz, first(s), size(s), feat);
+    for (int s = s0; s < s0 + kGroup; ++s)
+        if (size(s) > 64) centroid_rows(xyz, first(s), first(s) + size(s), feat, tile);
+}
+
 // Neighbours and row entries of atoms [a0, a0 + 16), four per wavefront.  A
 // lane takes one candidate of 64 at a time for each of the four atoms; those
 // not farther than an atom's 16th nearest so far go to its queue in LDS.  Once
@@ -247,7 +283,8 @@ __device__ void centroid_rows(const double* __restrict__ xyz, int j0, int j1, ui
 constexpr int kKnnAtoms = 4;                         // atoms per wavefront: one per row of 16 lanes
 constexpr int kKnnQueue = 64 + 16;                   // candidates waiting per atom: at most 15 + 64
 
-__device__ void neighbor_rows(const double* __restrict__ xyz, const double* __restrict__ q,
+template <bool MANY>
+__device__ __forceinline__ void neighbor_rows(const double* __restrict__ xyz, const double* __restrict__ q,
                               const double* __restrict__ sig, const double* __restrict__ eps,
                               const int32_t* __restrict__ sys_first, const int32_t* __restrict__ atom_sys, int a0,
                               int n_total, uint16_t* __restrict__ feat, int32_t* __restrict__ nbr,
@@ -343,7 +380,9 @@ __device__ void neighbor_rows(const double* __restrict__ xyz, const double* __re
         __syncthreads();
         load(step + 2, v);
         // first pass: which 64 candidates may hold one for any of the four atoms
-        unsigned hit = 0;
+        // (where a window of candidates is one 64: that one)
+        unsigned hit = MANY && n_c <= 64 ? 1u : 0u;
+        if (!MANY || hit == 0)
 #pragma unroll
         for (int no = 0; no < kKnnTile / 64; ++no) {
             const double* p = tile[buf] + 3 * (no * 64 + lane);
@@ -445,7 +484,9 @@ __device__ void neighbor_rows(const double* __restrict__ xyz, const double* __re
     }
 }
 
-// Grid: n_sys centroid workgroups, then one per 4 * kKnnAtoms atoms.
+// Grid: the centroid workgroups, one per system (MANY: per kGroup systems), then
+// one per 4 * kKnnAtoms atoms.
+template <bool MANY>
 __global__ void __launch_bounds__(256) k_features(const double* __restrict__ xyz, const double* __restrict__ q,
                                                   const double* __restrict__ sig, const double* __restrict__ eps,
                                                   const int32_t* __restrict__ sys_first,
@@ -456,12 +497,14 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ xyz
     __shared__ double queue_d[4 * kKnnAtoms * kKnnQueue];
     __shared__ int queue_j[4 * kKnnAtoms * kKnnQueue];
     __shared__ __attribute__((aligned(4))) uint16_t rowbuf[4 * kKnnAtoms * FF_LEARN_FEATURES];
-    const int b = blockIdx.x;
-    if (b < n_sys)
-        centroid_rows(xyz, sys_first[b], sys_first[b + 1], feat, tile);
+    const int b = blockIdx.x, centroids = MANY ? (n_sys + kGroup - 1) / kGroup : n_sys;
+    if (b >= centroids)
+        neighbor_rows<MANY>(xyz, q, sig, eps, sys_first, atom_sys, (b - centroids) * 4 * kKnnAtoms, n_total, feat, nbr,
+                            tile, queue_d, queue_j, rowbuf);
+    else if (MANY)
+        centroid_group(xyz, sys_first, b * kGroup, n_sys, feat, tile);
     else
-        neighbor_rows(xyz, q, sig, eps, sys_first, atom_sys, (b - n_sys) * 4 * kKnnAtoms, n_total, feat, nbr, tile,
-                      queue_d, queue_j, rowbuf);
+        centroid_rows(xyz, sys_first[b], sys_first[b + 1], feat, tile);
 }
 
 // ------------------------------------------------------------------ GEMM
@@ -1305,9 +1348,13 @@ ff_status ff_learn_features(int32_t n_sys, int32_t n_total, const double* xyz, c
     g_learn_err.clear();
     if (n_sys < 1 || n_total < 1) return lfail(FF_ERR_ARG, "need at least one system and one atom");
     if (!xyz || !q || !sigma || !eps || !sys_first || !atom_sys || !features) return lfail(FF_ERR_ARG, "null pointer");
-    const int blocks = n_sys + (n_total + 4 * kKnnAtoms - 1) / (4 * kKnnAtoms);
-    hipLaunchKernelGGL(k_features, dim3(blocks), dim3(256), 0, (hipStream_t)stream, xyz, q, sigma, eps,
-                       sys_first, atom_sys, n_sys, n_total, features, neighbors);
+    // many small systems are more centroid workgroups than the chip holds at a
+    // time beside the others (five a CU): 3,000 systems of three atoms take
+    // 18.6 us with a workgroup each, 10.0 in groups; 64 of 63 atoms 11.8 and 14.1
+    const bool many = n_sys >= 640 && n_total <= 16LL * n_sys;
+    const int blocks = (many ? (n_sys + kGroup - 1) / kGroup : n_sys) + (n_total + 4 * kKnnAtoms - 1) / (4 * kKnnAtoms);
+    hipLaunchKernelGGL(many ? k_features<true> : k_features<false>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, xyz,
+                       q, sigma, eps, sys_first, atom_sys, n_sys, n_total, features, neighbors);
     L_TRY(hipGetLastError());
     return FF_OK;
 }

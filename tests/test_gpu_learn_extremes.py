@@ -68,3 +68,25 @@ def test_features_go_to_any_16_bit_address(n, shift):
     end = shift + n * L.FEATURES
     np.testing.assert_array_equal(got[shift:end].reshape(n, L.FEATURES), _oracle(s)[0])
     assert (got[:shift] == 0x1234).all() and (got[end:] == 0x1234).all()
+
+
+# from 640 systems of at most 16 atoms on average 16 share a centroid workgroup:
+# by 16 lanes up to 16 atoms, a wavefront up to 64, the whole workgroup above
+@pytest.mark.parametrize("sizes", [(1,) * 640, (3,) * 400 + (700,) + (1, 2) * 130, (16,) * 641, (16,) * 639,
+                                   (15, 16, 17, 1) * 4 + (3,) * 320 + (64, 65) + (2,) * 333, (2, 64, 66, 20) * 2])
+@pytest.mark.parametrize("kind", ["normal", "symmetric", "offset"])
+def test_features_of_many_small_systems(sizes, kind):
+    systems = []
+    for k, n in enumerate(sizes):
+        x = np.random.default_rng([n, k]).normal(scale=8.0, size=(n, 3))
+        if kind == "symmetric":                 # centroid at an atom or between two, whose offsets nearly vanish
+            x[n // 2:] = -x[: n - n // 2]
+        systems.append(_system(x + (3.0e7 if kind == "offset" else 0.0), k))
+    sa = L.SystemArrays(systems, DEV)
+    x = np.concatenate([s["x"] for s in systems])
+    print(f"features of {len(sizes)} systems, {kind}", flush=True)
+    f, nb = L.features(sa, torch.tensor(x, device=DEV), want_neighbors=True)
+    cat = lambda k: np.concatenate([s[k] for s in systems])  # noqa: E731
+    fo, nbo = OL.features(x, cat("q"), cat("sigma"), cat("eps"), sa.sys_first_host)
+    np.testing.assert_array_equal(nb.cpu().numpy(), nbo)
+    np.testing.assert_array_equal(f.cpu().numpy().view(np.uint16), fo)
