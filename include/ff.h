@@ -181,8 +181,11 @@ int32_t ff_batch_size(const ff_ctx *ctx);
  * j-tiles (at least one) goes to one-tile chunks that end the launch, so that
  * it drains on short workgroups.  FP64 chunks of one tile are cut into halves
  * or quarters of a tile in systems too small to fill the chip with whole ones.
- * A tile configuration fixes the block size
- * and the wavefronts and i-atoms per lane of the FP32 and FP64 kernels.
+ * Shorter chunks take more workspace (partial sums of each): up to 1.3 MiB for
+ * the parts of a tile, up to 44 MiB for the one-tile FP64 chunks that batches
+ * below 20,000 tiles get by default instead of chunks of four.
+ * A tile configuration fixes the block size and the wavefronts and i-atoms per
+ * lane of the FP32 and FP64 kernels.
  * ff_create / ff_create_batch choose one from the system sizes; the
  * functions below name one explicitly.  The tiling changes only speed and the
  * summation order of the pair partials (results agree to rounding). */

@@ -44,9 +44,11 @@ extern "C" {
 int32_t ff_learn_param_count(void);
 
 /* Device workspace for ff_learn_forward and ff_learn_backward with up to
- * n_rows rows (the backward pass keeps its partial sums of the gradient there;
- * with arrays that its fused kernels cannot read, activations, their
- * gradients and 4 MiB of per-slice partial sums).  0 for n_rows < 1. */
+ * n_rows rows.  The backward pass keeps its partial sums of the gradient there.
+ * Where arrays are not aligned for the fused kernels (features and params_bf16
+ * to 8 bytes, the output to 16), it holds activations, their gradients and
+ * 4 MiB of per-slice partial sums; the forward pass uses it only then.
+ * 0 for n_rows < 1. */
 size_t ff_learn_workspace_bytes(int32_t n_rows);
 
 /* Description of the last error of an ff_learn_* call on this thread. */
@@ -96,8 +98,9 @@ ff_status ff_learn_forward(const float *params, const uint16_t *params_bf16, con
  * c < 3 of (Y_ic - target_ic)^2, target [n_rows][3] FP32 (device).  grad
  * (FP32, packed like params, device) is overwritten with d loss / d params,
  * computed from BF16 copies of the forward activations and of the output
- * and hidden-layer gradients, FP32 accumulation; bias gradients are FP32
- * column sums; the weight gradients sum their k slices in a fixed order.
+ * and hidden-layer gradients, FP32 accumulation; bias gradients and the loss
+ * are FP64 sums, rounded once; the weight gradients add FP32 partial sums of
+ * blocks of rows in a fixed order, in FP64.
  * loss: one FP32 on the device.  workspace: device, 256-byte aligned, at
  * least ff_learn_workspace_bytes(n_rows). */
 ff_status ff_learn_backward(const float *params, const uint16_t *params_bf16, const uint16_t *features,

@@ -126,11 +126,6 @@ static void far_exclusions(const ff_system& s, int aoff, FarTmp& ft) {
         for (int a = 0; a < s.n_angles; ++a) add(s.angle[3 * a], s.angle[3 * a + 2]);
 }
 
-// Tile configuration: explicit (cfg >= 0, chunk >= 1), or by default a single
-// system picks its I-block by size and a batch of several systems uses 64-atom
-// I-blocks so that small systems are padded to a multiple of 64 only.
-// `sys` receives n_sys entries; `ft` the far pairs and their units.
-// energy_only: no optimizer vectors (the layout serves ff_energy_grad only).
 // The chunks of one I-block with T j-tiles: `full` chunks of c tiles, one of
 // `rem` (< c) tiles if rem > 0, then `tail` one-tile chunks (c > 1 only).
 struct RowSplit {
@@ -171,6 +166,10 @@ static int row_chunks64(const Layout& L, int T) {
     return L.split < kParts ? T * (kParts / L.split) : row_split(T, L.chunk[1]).count();
 }
 
+// Tile configuration: explicit (cfg_req >= 0, chunk_req >= 1), or the default for
+// the systems' sizes.  `sys` receives n_sys entries; `ft` the far pairs and
+// their units.  energy_only: no optimizer vectors (the layout serves
+// ff_energy_grad only).
 static bool make_layout(const ff_system* s, int32_t n_sys, int32_t m_max, Layout& L, SysInfo* sys, FarTmp& ft,
                         int32_t cfg_req = -1, int32_t chunk_req = 0, int32_t chunk64_req = 0,
                         bool energy_only = false) {
@@ -900,14 +899,14 @@ ff_status ff_energy_grad_noalloc(const ff_system* sys, const double* xyz, double
 
 static constexpr int kCyclesPerGraph = 4;
 
-// with32 = false leaves the FP32 pair kernel out: FP64 runs, and FP32-mode
-// runs once every system has switched to FP64 (the switch is final).
 // Graphs in a batch: one for each kBatchShare that went out before, so that the
 // cycles run for nothing after the last system is done stay a small share of
 // the run.  (Synchronizing after batches of 1, 2, 4, ... 16 graphs, a run of 62
 // cycles took 124: L-BFGS of 512 atoms 2.79 ms, 2.34 this way.)
 static constexpr uint32_t kBatchShare = 16, kMaxBatch = 16;
 
+// with32 = false leaves the FP32 pair kernel out: FP64 runs, and FP32-mode
+// runs once every system has switched to FP64 (the switch is final).
 static ff_status build_graph(ff_ctx* c, bool with32, hipGraphExec_t* out) {
     hipStream_t st = c->own;
     Args a{};

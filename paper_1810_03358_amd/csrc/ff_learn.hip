@@ -1111,8 +1111,9 @@ __global__ void __launch_bounds__(256, 1) k_train_block(const float* __restrict_
 
 // Gradient and loss from the workgroups' partial sums, added in FP64 in a fixed
 // order.  A workgroup takes 128 entries: eight groups of 32 threads take four
-// entries each (16-byte loads) of an eighth of the partials; the last
-// workgroup sums the biases and the loss.
+// entries each (16-byte loads) of an eighth of the partials.  The entries of a
+// workgroup are all weights (FP32 partials) or all biases (FP64; the last
+// workgroup's: b3 and the loss).
 constexpr int kSumEntries = 128;
 static_assert(kB1 % kSumEntries == 0 && kW2 % kSumEntries == 0 && kB2 % kSumEntries == 0 && kW3 % kSumEntries == 0 &&
               kB3 % kSumEntries == 0, "a workgroup's entries are all weights or all biases");

@@ -181,11 +181,11 @@ __device__ __forceinline__ double get_partial(const double* p) {
 // has put the workgroup's partials before).  It goes on with the reduction,
 // instead of a launch of its own.  No workgroup counts before all of its
 // wavefronts are here: the last one rewrites the control block that they read
-// on their way.  The partials are in memory once their
-// stores are acknowledged, so the counter needs no release, which would write
-// back the XCD's whole L2 from every workgroup.  FP64 evaluations with the
-// launch, with the last workgroup, and with a release: 512 atoms 17.0, 16.0,
-// 15.8 us; 96 chains of 200-4,000 atoms 205, 206, 248 us.
+// on their way.  The partials are in memory once their stores are acknowledged,
+// so the counter needs no release, which would write back the XCD's whole L2
+// from every workgroup.  FP64 evaluations with the launch, with the last
+// workgroup, and with a release: 512 atoms 17.0, 16.0, 15.8 us; 96 chains of
+// 200-4,000 atoms 205, 206, 248 us.
 __device__ __forceinline__ bool last_workgroup(uint32_t* ticket, int n) {
     __shared__ int last;
     __syncthreads();
@@ -292,17 +292,17 @@ __device__ __forceinline__ double energy_share(const Args& a, const SysInfo& si,
     return e;
 }
 
+// The decision of k_finalize's last workgroup is a call: inlined, it costs the
+// gather of every tile registers and 96 chains of 200-4,000 atoms 1 % of an
+// evaluation.
+__device__ __attribute__((noinline)) void decide(CtlState* c) { after_eval(c); }
+
 // One workgroup per 64-atom tile of a system: gradient = pair partials of
 // the tile (gather_tile) + the bonded-term slots of each atom (staged through
 // LDS, added in slot order).  Per-workgroup partials: max |g|, |g|^2,
 // optionally <g_base, d>, and a share of the pair-workgroup and bonded-block
 // energies, which the system's last workgroup adds up.  Grid: every tile of
-// every system
-// (flat, map_fin).
-// (The decision is a call: inlined, it costs the gather of every tile registers
-// and 96 chains of 200-4,000 atoms 1 % of an evaluation.)
-__device__ __attribute__((noinline)) void decide(CtlState* c) { after_eval(c); }
-
+// every system (flat, map_fin).
 __global__ void __launch_bounds__(kFinBlock) k_finalize(Args a) {
     const Layout& L = a.L;
     const int2 mb = at<int2>(a.ws, L.off_map_fin)[blockIdx.x];

@@ -70,11 +70,8 @@ __device__ __forceinline__ void load_pos(const double* X, int32_t atom, int32_t 
 }
 
 // ------------------------------------------------------------------ bonded
-// One thread per bond, angle or dihedral; FP64.  The gradient of each term
-// on each of its atoms goes to its own slot (no scatter), the energy to a
-// per-block partial.
-// Energy of bonded term t (bonds, then angles, then dihedrals) and its
-// gradient on each of its atoms, written to the term's own slots.
+// Energy of bonded term t (bonds, then angles, then dihedrals; FP64) and its
+// gradient on each of its atoms, written to the term's own slots (no scatter).
 __device__ double bonded_term(const Args& a, const double* X, const SysInfo& si, int t) {
     const Layout& L = a.L;
     double e = 0.0;
@@ -584,8 +581,10 @@ __device__ __forceinline__ void tile64(const double4* __restrict__ s_xq, const d
                                        double& fjx, double& fjy, double& fjz, double& elj, double& ecs) {
     double4 pn = s_xq[lane + s0];
     double2 cn = s_c[lane + s0];
-    // the loop without masks starts in the middle of a 64-byte block (50,000
-    // atoms: 1,440 us; 1,443 at its start, 1,445 where the compiler puts it)
+    // the loop without masks starts in the middle of a 64-byte block: 0.4 % less
+    // per evaluation than where the compiler puts it, in the median over 512 to
+    // 60,000 atoms (512 atoms: 14.94 us against 15.00; at 50,000, 1,345 and 1,346,
+    // the 1-2 % between runs hide it)
     if (!MASKED) asm volatile(".p2align 6\n.rept 8\ns_nop 0\n.endr");
 #pragma unroll 1
     for (int sp = s0; sp < s1; sp += kPartSteps) {
